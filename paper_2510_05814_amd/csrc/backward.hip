@@ -6,9 +6,8 @@
 // tile_math.h).  Pixels outside the ellipse or the kernel's blocks contribute nothing
 // (Sec. IV-B).
 //
-// Work split: one wave per 16x16 block.  Per kernel the wave's per-lane sums are reduced over
-// the block's 256 pixels by a transposed butterfly (cross-half swaps, then DPP) into one
-// per-(block, kernel) partial row.  A second pass sums each kernel's partial rows over its
+// Work split: one wave per 16x16 block, four kernels of its list at a time, 16 lanes each; a
+// reduction inside the 16 lanes (DPP) leaves one per-(block, kernel) partial row.  A second pass sums each kernel's partial rows over its
 // blocks in row-major block order.  Every order is fixed: gradients are bitwise
 // reproducible and no atomics are used.
 #include "tile_math.h"
@@ -31,38 +30,42 @@ struct BackwardArgs {
 
 template <int C, int ORDER, bool RBF>
 __global__ __launch_bounds__(kWave) void k_backward(BackwardArgs a) {
-  __shared__ float4 srec[kChunk * record_stride(C, ORDER) / 4];
+  __shared__ PixelSeed<C> seeds[kTilePixels];
+  __shared__ __align__(16) BackwardScratch sc;
   const int tile = xcd_block(blockIdx.x, a.S.T);
   const SegGrid sg = seg_of_tile(a.S, tile);
   const PixelCoords px = lane_pixels(sg, tile - sg.tile_offset);
+  const int lane = threadIdx.x & 63;
   // MSE of this raster: dL/dy = 2 (y - t) / (W H C)
   const float inv_n2 = 2.0f / ((float)sg.W * (float)sg.H * (float)C);
-  PixelSeed<C> sd;
 #pragma unroll
   for (int i = 0; i < kRows; ++i) {
     const int v = px.v0 + 4 * i;
-    sd.valid[i] = false;
-    sd.invD[i] = 0.0f;
-    sd.gy[i] = 0.0f;
+    PixelSeed<C> sd;
+    sd.gy = 0.0f;
 #pragma unroll
-    for (int c = 0; c < C; ++c) sd.g[i][c] = 0.0f;
+    for (int c = 0; c < C; ++c) sd.g[c] = 0.0f;
     if (in_raster(px.u, v, sg)) {
       const size_t p = (size_t)sg.pixel_offset + (size_t)v * sg.W + px.u;
       const float D = a.denom[p];
       if (D > 0.0f) {
-        sd.valid[i] = true;
-        sd.invD[i] = RBF ? 1.0f : __builtin_amdgcn_rcpf(D);
+        const float invD = RBF ? 1.0f : __builtin_amdgcn_rcpf(D);
 #pragma unroll
         for (int c = 0; c < C; ++c) {
           const float yc = a.image[p * C + c];
-          sd.g[i][c] = a.target ? (yc - a.target[p * C + c]) * inv_n2 : a.grad_image[p * C + c];
-          if (!RBF) sd.gy[i] = __builtin_fmaf(sd.g[i][c], yc, sd.gy[i]);
+          const float g = a.target ? (yc - a.target[p * C + c]) * inv_n2 : a.grad_image[p * C + c];
+          if (!RBF) sd.gy = __builtin_fmaf(g, yc, sd.gy);
+          sd.g[c] = g * invD;
         }
+        sd.gy = sd.gy * invD;
       }
     }
+    seeds[((lane >> 4) + 4 * i) * kTile + (lane & 15)] = sd;
   }
-  backward_accumulate<C, ORDER>(px, a.S.r2, a.records, a.vals, 0, false, a.ranges[tile], srec,
-                                false, 0ull, sd, a.pair_grads);
+  const float2 o = block_base(sg, tile - sg.tile_offset);
+  backward_accumulate<C, ORDER, false>(block_box(sg, tile - sg.tile_offset), o.x, o.y, sg.inv_s,
+                                       a.S.r, a.S.r2, a.records, a.vals, 0, false, a.ranges[tile],
+                                       seeds, sc, false, a.pair_grads);
 }
 
 struct GatherArgs {

@@ -43,8 +43,10 @@ template <int C, int ORDER, bool RBF, int TRUNC>
 __global__ __launch_bounds__(kWave) void k_fit_tile(FitTileArgs a) {
   constexpr int LDS_FLOATS = kChunk * record_stride(C, ORDER);
   static_assert(LDS_FLOATS >= 64, "the rank sort's scratch lives in the record buffer");
-  __shared__ float4 srec[LDS_FLOATS / 4];
-  __shared__ uint32_t s_ent[kChunk];  // the entries of the chunk being staged
+  // the forward's records, then the backward's pixel seeds
+  constexpr int LDS_BYTES = max_of(LDS_FLOATS * 4, kTilePixels * (int)sizeof(PixelSeed<C>));
+  __shared__ float4 srec[LDS_BYTES / 16];
+  __shared__ __align__(16) BackwardScratch sc;  // sc.ent: also the entries of the chunk being staged
   const int tile = xcd_block(blockIdx.x, a.S.T);
   const int t0 = a.status[kStepShadow];
   // The bucket's fill count; the cursor is then reset for the next step's scatter (the store
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(kWave) void k_fit_tile(FitTileArgs a) {
   // ranked in registers and kept in LDS for the forward's staging.
   constexpr int run = LDS_FLOATS >= 1024 ? 1024 : (LDS_FLOATS >= 512 ? 512 : 256);
   if (rg.y - rg.x <= kChunk) {
-    rank_sort64(a.vals + rg.x, rg.y - rg.x, reinterpret_cast<uint32_t*>(srec), s_ent);
+    rank_sort64(a.vals + rg.x, rg.y - rg.x, reinterpret_cast<uint32_t*>(srec), sc.ent);
   } else {
     sort_bucket(a.vals + rg.x, a.vals_alt + rg.x, rg.y - rg.x, reinterpret_cast<uint32_t*>(srec),
                 run);
@@ -80,20 +82,20 @@ __global__ __launch_bounds__(kWave) void k_fit_tile(FitTileArgs a) {
 
   const PixelCoords px = lane_pixels(sg, tile - sg.tile_offset);
   float D[kRows], N[kRows][C];
-  uint64_t live = 0;
   forward_accumulate<C, ORDER, TRUNC>(px, a.S.r2, a.S.cut_scale, a.S.cut_offset, a.records,
-                                      a.vals, a.shift, rg, srec, D, N, live, s_ent);
+                                      a.vals, a.shift, rg, srec, D, N, sc.ent);
 
-  PixelSeed<C> sd;
+  const int lane = threadIdx.x & 63;
+  PixelSeed<C>* seeds = reinterpret_cast<PixelSeed<C>*>(srec);
+  __syncthreads();  // the records are read: their place takes the seeds
   float err = 0.0f;
 #pragma unroll
   for (int i = 0; i < kRows; ++i) {
     const int v = px.v0 + 4 * i;
-    sd.valid[i] = false;
-    sd.invD[i] = 0.0f;
-    sd.gy[i] = 0.0f;
+    PixelSeed<C> sd;
+    sd.gy = 0.0f;
 #pragma unroll
-    for (int c = 0; c < C; ++c) sd.g[i][c] = 0.0f;
+    for (int c = 0; c < C; ++c) sd.g[c] = 0.0f;
     if (in_raster(px.u, v, sg)) {
       const size_t p = (size_t)sg.pixel_offset + (size_t)v * sg.W + px.u;
       const bool cov = D[i] > 0.0f;
@@ -107,21 +109,24 @@ __global__ __launch_bounds__(kWave) void k_fit_tile(FitTileArgs a) {
         const float d = yc - a.target[p * C + c];
         err = __builtin_fmaf(d, d, err);
         if (cov) {
-          sd.g[i][c] = d * inv_n2;
-          if (!RBF) sd.gy[i] = __builtin_fmaf(sd.g[i][c], yc, sd.gy[i]);
+          const float g = d * inv_n2;
+          if (!RBF) sd.gy = __builtin_fmaf(g, yc, sd.gy);
+          sd.g[c] = g * invD;
         }
       }
       if (a.image) a.denom[p] = D[i];
-      sd.valid[i] = cov;
-      sd.invD[i] = invD;
+      sd.gy = sd.gy * invD;
     }
+    seeds[((lane >> 4) + 4 * i) * kTile + (lane & 15)] = sd;
   }
   for (int off = 32; off > 0; off >>= 1) err += __shfl_xor(err, off);
   if (threadIdx.x == 0) a.tile_loss[tile] = err * inv_n;
 
   // each partial row goes to the row its entry names, where Adam reads it
-  backward_accumulate<C, ORDER>(px, a.S.r2, a.records, a.vals, a.shift, true, rg, srec, true,
-                                live, sd, a.pair_grads, a.S.K);
+  const float2 o = block_base(sg, tile - sg.tile_offset);
+  backward_accumulate<C, ORDER, true>(block_box(sg, tile - sg.tile_offset), o.x, o.y, 1.0f, a.S.r,
+                                      a.S.r2, a.records, a.vals, a.shift, true, rg, seeds, sc, true,
+                                      a.pair_grads, a.S.K);
 }
 
 struct AdamFitArgs {

@@ -80,9 +80,8 @@ __global__ __launch_bounds__(kWave) void k_render(RenderArgs a) {
   const SegGrid sg = seg_of_tile(a.S, tile);
   const PixelCoords px = lane_pixels(sg, tile - sg.tile_offset);
   float D[kRows], N[kRows][C];
-  uint64_t live;
   forward_accumulate<C, ORDER, TRUNC>(px, a.S.r2, a.S.cut_scale, a.S.cut_offset, a.records,
-                                      a.vals, 0, rg, srec, D, N, live);
+                                      a.vals, 0, rg, srec, D, N);
   render_epilogue<C, RBF>(a, sg, px, tile, D, N);
 }
 

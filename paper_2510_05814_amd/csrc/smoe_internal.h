@@ -29,6 +29,7 @@ __host__ __device__ constexpr int record_stride(int C, int order) {
   return (7 + expert_floats(C, order) + 3) & ~3;
 }
 constexpr int kRecExpert = 7;
+__host__ __device__ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 
 // The rasters of one call.  A batched call (several images of a batched fit, or several
 // render requests) numbers the blocks of all its rasters consecutively (segment s owns

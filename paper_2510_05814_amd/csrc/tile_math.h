@@ -7,6 +7,8 @@
 // iteration i covers one 16x4 strip of the block.
 #pragma once
 
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace smoe {
@@ -73,6 +75,25 @@ __device__ __forceinline__ PixelCoords lane_pixels(const SegGrid& g, int tile) {
   return p;
 }
 
+// Coordinates of a block's first and last column and row (whole blocks, also where they hang
+// over the raster's edges).
+struct BlockBox {
+  float x0, x1, y0, y1;
+  float scale;  // rows per unit of y
+};
+__device__ __forceinline__ BlockBox block_box(const SegGrid& g, int tile) {
+  const int u = kTile * (g.bx0 + tile % g.ntx) - g.ox, v = kTile * (g.by0 + tile / g.ntx) - g.oy;
+  return BlockBox{sample_coord(u, g.ox, g.inv_s), sample_coord(u + kTile - 1, g.ox, g.inv_s),
+                  sample_coord(v, g.oy, g.inv_s), sample_coord(v + kTile - 1, g.oy, g.inv_s),
+                  (float)g.scale};
+}
+// o + 0.5 + (column, row) of the block's first pixel (exact): its pixel (c, r) samples
+// ((.x + c) * inv_s, (.y + r) * inv_s).
+__device__ __forceinline__ float2 block_base(const SegGrid& g, int tile) {
+  return make_float2((float)(kTile * (g.bx0 + tile % g.ntx)) + 0.5f,
+                     (float)(kTile * (g.by0 + tile / g.ntx)) + 0.5f);
+}
+
 // Stages the records of list entries [base, base + n) (n <= kChunk) into LDS.  An entry
 // holds the kernel id shifted left by `shift` (the fit step's packed bucket entries; 0
 // elsewhere).
@@ -115,20 +136,20 @@ __device__ __forceinline__ void stage_records_lds(float4* __restrict__ srec,
 // One list entry of the forward: adds its terms to D = sum pi K and N_c = sum pi K m_c of
 // the lane's four pixels that the render's rule keeps.  TRUNC == SMOE_TRUNC_RENDER: the
 // ellipse q <= r^2.  TRUNC == SMOE_TRUNC_GRADIENT (the block lists decide the render): every
-// term binary32 holds, i.e. whose exponent a = rho log2(e) - q log2(e)/2 is >= -125.  Returns
-// whether any of the lane's pixels passed the ellipse test q <= r2.  r: the entry's render
-// record; cut_scale, cut_offset: the render's bound in the compare-free form of Segs.
+// term binary32 holds, i.e. whose exponent a = rho log2(e) - q log2(e)/2 is >= -125.  r: the
+// entry's render record; cut_scale, cut_offset: the render's bound in the compare-free form of
+// Segs.
 //
 // Neither bound is a per-row compare: a VALU instruction that writes or reads a scalar
 // register (a compare's lane mask, a select on it) issues at about 60 % of the rate of one
-// on vector registers alone.  The ellipse test compares the minimum of the four rows' q
-// once; the render's bound goes through the exponent: with the ellipse, max(q, u) with
-// u = fma(q, cut_scale, cut_offset) is q inside the bound and gives a term beyond it an
-// exponent of about -2^36; with the representable range, min(a, fma(a, 2^60, 125 * 2^60)) is
-// a for a >= -125 and below -2^43 otherwise.  Either way exp2 of an excluded term is exactly
-// zero and every kept term carries the same bits as with a compare-and-select.
+// on vector registers alone.  The render's bound goes through the exponent: with the
+// ellipse, max(q, u) with u = fma(q, cut_scale, cut_offset) is q inside the bound and gives a
+// term beyond it an exponent of about -2^36; with the representable range, min(a, fma(a,
+// 2^60, 125 * 2^60)) is a for a >= -125 and below -2^43 otherwise.  Either way exp2 of an
+// excluded term is exactly zero and every kept term carries the same bits as with a
+// compare-and-select.
 template <int C, int ORDER, int TRUNC>
-__device__ __forceinline__ bool forward_entry(const PixelCoords& px, float r2, float cut_scale,
+__device__ __forceinline__ void forward_entry(const PixelCoords& px, float r2, float cut_scale,
                                               float cut_offset, const float* r, float (&D)[kRows],
                                               float (&N)[kRows][C]) {
   // Truncation test: the binary32 sequence of the ABI contract (no contraction).
@@ -185,12 +206,6 @@ __device__ __forceinline__ bool forward_entry(const PixelCoords& px, float r2, f
       N[i][c] = __builtin_fmaf(e, m, N[i][c]);
     }
   }
-  static_assert(kRows == 4, "the ellipse test takes the minimum of four rows");
-  // q >= +0 (a sum of squares, or the bound's larger stand-in), so the order of the floats is
-  // the order of their bit patterns as integers: no NaN handling in the minimum
-  const int qmin = min(min(__float_as_int(q[0]), __float_as_int(q[1])),
-                       min(__float_as_int(q[2]), __float_as_int(q[3])));
-  return __int_as_float(qmin) <= r2;
 }
 
 // A copy of x that the compiler must keep in a vector register: loop-invariant operands of
@@ -212,8 +227,6 @@ __device__ __forceinline__ void zero_sums(float (&D)[kRows], float (&N)[kRows][C
 
 // Forward accumulation over a block's list [rg.x, rg.y) in list order (forward_entry per
 // entry, records staged through LDS in chunks).
-// live: bit k set if any pixel of the block passed the ellipse test q <= r2 for entry k of
-// the last staged chunk (the only chunk for lists of up to kChunk entries).
 // shift: list entries hold the kernel id << shift.  ent: null, or LDS room for one chunk of
 // entries, which the staging then reads from there (a single-chunk list already holds them,
 // sorted; longer lists copy each chunk's entries in).
@@ -223,7 +236,7 @@ __device__ __forceinline__ void forward_accumulate(const PixelCoords& px, float 
                                                    const float* __restrict__ records,
                                                    const uint32_t* __restrict__ vals, int shift,
                                                    int2 rg, float4* srec, float (&D)[kRows],
-                                                   float (&N)[kRows][C], uint64_t& live,
+                                                   float (&N)[kRows][C],
                                                    uint32_t* ent = nullptr) {
   constexpr int RS = record_stride(C, ORDER);
   constexpr int Q = RS / 4;
@@ -234,62 +247,15 @@ __device__ __forceinline__ void forward_accumulate(const PixelCoords& px, float 
     const int n = min(kChunk, rg.y - base);
     if (ent) stage_records_lds<RS>(srec, records, vals, base, n, shift, ent, rg.y - rg.x <= kChunk);
     else stage_records<RS>(srec, records, vals, base, n, shift);
-    live = 0;
-    for (int k = 0; k < n; ++k) {
-      const float* r = reinterpret_cast<const float*>(&srec[k * Q]);
-      if (__any(forward_entry<C, ORDER, TRUNC>(px, r2, cut_scale, cut_offset, r, D, N)))
-        live |= 1ull << k;
-    }
+    for (int k = 0; k < n; ++k)
+      forward_entry<C, ORDER, TRUNC>(px, r2, cut_scale, cut_offset,
+                                     reinterpret_cast<const float*>(&srec[k * Q]), D, N);
   }
 }
 
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
-}
-
-// Transposed wave reduction of 16 values: on return lane l holds the sum over all 64 lanes
-// of v[(l >> 2) & 15].  Each stage pairs every lane with one whose index differs in the next
-// bit (5, 4, 3, 2); a lane keeps the half of its values selected by that bit and adds the
-// partner's copy of the same half, halving the values per lane.  Bits 1 and 0 are then a
-// plain butterfly.  About 40 instructions for 16 sums instead of 6 per sum.
-__device__ __forceinline__ float wave_reduce16_transposed(float (&v)[16]) {
-  const int lane = threadIdx.x & 63;
-  // bit 5: v_permlane32_swap exchanges lanes 32-63 of its first operand with lanes 0-31 of
-  // its second, so (a + b) of the two results holds sum(v[i]) in the low half and
-  // sum(v[i + 8]) in the high half.
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]),
-                                                    false, false);
-    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  // bit 4: v_permlane16_swap exchanges the odd 16-lane rows of its first operand with the
-  // even rows of its second.
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 4]),
-                                                    false, false);
-    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  // bit 3: DPP row_ror:8 pairs lane l with l ^ 8 inside each row of 16.
-  const bool b3 = (lane & 8) != 0;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const float keep = b3 ? v[i + 2] : v[i];
-    const float send = b3 ? v[i] : v[i + 2];
-    v[i] = keep + dpp<0x128>(send);
-  }
-  // bit 2: DPP row_half_mirror pairs lane l with 7 - l inside each group of 8.
-  const bool b2 = (lane & 4) != 0;
-  {
-    const float keep = b2 ? v[1] : v[0];
-    const float send = b2 ? v[0] : v[1];
-    v[0] = keep + dpp<0x141>(send);
-  }
-  v[0] += dpp<0x4E>(v[0]);  // quad_perm [2, 3, 0, 1]: bit 1
-  v[0] += dpp<0xB1>(v[0]);  // quad_perm [1, 0, 3, 2]: bit 0
-  return v[0];
 }
 
 // Transposed reduction inside each 16-lane row: on return lane l holds the sum over the
@@ -430,25 +396,129 @@ __device__ __forceinline__ float finish_gradient(float s, bool live, float slope
   return live && i < 2 ? s - ex : s;
 }
 
-// Adjoint seed of one pixel: dL/dy (g), 1/D, sum_c g_c y_c; `valid` false where D = 0 or the
-// pixel lies outside the raster (no gradient flows there).  With the seed 1/D -> 1 and
+// The sum over each 16-lane row of 16 values, as row_reduce16_transposed (lane l ends with the
+// row's sum of v[l & 15]), for values the caller has just computed.  The first two stages add
+// with the DPP lane mask doing the selection: for the pair (v[i], v[i + 8]) one add leaves
+// v[i] + v[i](l ^ 8) in every lane and a second, written only to lanes 8-15 of the row
+// (bank_mask 0xc), replaces it there by v[i + 8] + v[i + 8](l ^ 8) -- two 4-cycle adds per pair
+// instead of two selects and an add.  DPP reads of a register need two wait states after
+// its write, which nothing inserts inside an asm block: the leading and trailing s_nop and the
+// order of the adds (a register is read at least five instructions after its write) give
+// them.  Every lane of the wave must be active.
+__device__ __forceinline__ float row_reduce16_masked(float (&v)[16]) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %8, %8 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %10, %10 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %3, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %4, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %12, %12 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %5, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %13, %13 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %6, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %14, %14 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %7, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %7, %15, %15 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %3, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "s_nop 1"
+      : "+&v"(v[0]), "+&v"(v[1]), "+&v"(v[2]), "+&v"(v[3]), "+&v"(v[4]), "+&v"(v[5]), "+&v"(v[6]),
+        "+&v"(v[7])
+      : "v"(v[8]), "v"(v[9]), "v"(v[10]), "v"(v[11]), "v"(v[12]), "v"(v[13]), "v"(v[14]),
+        "v"(v[15]));
+  const int lane = threadIdx.x & 63;
+  const bool b1 = (lane & 2) != 0, b0 = (lane & 1) != 0;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float keep = b1 ? v[i + 2] : v[i], send = b1 ? v[i] : v[i + 2];
+    v[i] = keep + dpp<0x4E>(send);
+  }
+  const float keep = b0 ? v[1] : v[0], send = b0 ? v[0] : v[1];
+  return keep + dpp<0xB1>(send);
+}
+
+// Adjoint seeds of a block's pixels in LDS, row-major: dL/dy_c / D and sum_c dL/dy_c y_c / D,
+// zero where no gradient flows (D = 0 or outside the raster).  With the seed 1/D -> 1 and
 // sum_c g_c y_c -> 0 the same backward is the adjoint of the un-normalised sum of Eq. (1):
 // then w = pi K is dy_c/dm_c and G = sum_c g_c m_c is dL/d(pi K).
 template <int C>
-struct PixelSeed {
-  float g[kRows][C];
-  float invD[kRows];
-  float gy[kRows];
-  bool valid[kRows];
+struct alignas(C == 3 ? 16 : 8) PixelSeed {
+  float g[C];
+  float gy;
 };
 
-// Backward over a block's list [rg.x, rg.y): for every kernel the wave forms, per pixel, the
-// adjoints of its 6 + 3C raw parameters (recomputing pi K from the record, w = pi K / D),
-// sums them over the block's 256 pixels with the transposed reduction, and writes the
-// per-(block, kernel) partial row pair_grads[list position].  `staged`: the records of a
-// single-chunk list are already in srec and `live` holds the forward's per-entry hits (the
-// fused fit kernel rendered from them): an entry no pixel passed gets a zero row without
-// repeating its tests -- the row it would reduce to, bit for bit.
+// The rows [row0, row1] and columns [col0, col1] (of 0..15; empty when row0 > row1) of a block
+// that hold every pixel inside the ellipse q <= r^2 of one kernel.  In z1 = (x - mu_x) / l11
+// the ellipse's upper edge l21 z1 + l22 sqrt(r^2 - z1^2) is concave, its lower edge convex, so
+// over the block's columns each reaches furthest at its extremum clamped to them; the left
+// and right edges over the block's rows alike.  r is widened by 1e-3 of itself and by what the
+// rounding of dy - l21 z1 can move z2 = (dy - l21 z1) / l22 by, and the edges by a hundredth of
+// a pixel and the rounding of the coordinates, far above the error of the binary32 test and
+// of this; kernels whose factors leave binary32's comfortable range, and
+// whatever compares as not a number, keep the whole block.
+struct EllipseBox {
+  int row0, row1, col0, col1;
+};
+__device__ __forceinline__ EllipseBox ellipse_box(const BlockBox& bb, float r, float mux, float muy,
+                                                  float i11, float l21, float i22) {
+  const float l11 = __builtin_amdgcn_rcpf(i11), l22 = fabsf(__builtin_amdgcn_rcpf(i22));
+  const float dx0 = bb.x0 - mux, dx1 = bb.x1 - mux, d0 = bb.y0 - muy, d1 = bb.y1 - muy;
+  const float za = fminf(dx0 * i11, dx1 * i11), zb = fmaxf(dx0 * i11, dx1 * i11);
+  const float zmax = fminf(fmaxf(fabsf(za), fabsf(zb)), 1.001f * r);
+  const float rr =
+      1.001f * r + 1e-6f * (fmaxf(fabsf(d0), fabsf(d1)) + fabsf(l21) * zmax) * fabsf(i22);
+  const float syy = l21 * l21 + l22 * l22;
+  const float is = __builtin_amdgcn_rsqf(syy);
+  EllipseBox e{0, 15, 0, 15};
+  if (!(syy > 1e-24f && syy < 1e24f && fabsf(l11) > 1e-12f && fabsf(l11) < 1e12f && rr < 1e9f))
+    return e;
+  // rows: over z1 in [za, zb] cut to [-rr, rr]
+  const float zl = fmaxf(za, -rr), zh = fminf(zb, rr);
+  const float zs = rr * l21 * is;  // where the upper edge peaks; the lower edge's is -zs
+  const float zu = fminf(fmaxf(zs, zl), zh), zd = fminf(fmaxf(-zs, zl), zh);
+  const float up = l21 * zu + l22 * __builtin_amdgcn_sqrtf(fmaxf(rr * rr - zu * zu, 0.0f));
+  const float dn = l21 * zd - l22 * __builtin_amdgcn_sqrtf(fmaxf(rr * rr - zd * zd, 0.0f));
+  const float my = 0.01f + 3e-7f * fmaxf(fabsf(bb.y0), fabsf(bb.y1)) * bb.scale;
+  const float t0 = (dn - d0) * bb.scale - my, t1 = (up - d0) * bb.scale + my;
+  // columns: over dy in [d0, d1] cut to the ellipse's own extent
+  const float ext = rr * syy * is;
+  const float dl = fmaxf(d0, -ext), dh = fminf(d1, ext);
+  const float ds = rr * l21;  // where the right edge peaks; the left edge's is -ds
+  const float du = fminf(fmaxf(ds, dl), dh), dd = fminf(fmaxf(-ds, dl), dh);
+  const float e2 = ext * ext, iss = is * is;
+  const float zr = (l21 * du + l22 * __builtin_amdgcn_sqrtf(fmaxf(e2 - du * du, 0.0f))) * iss;
+  const float zq = (l21 * dd - l22 * __builtin_amdgcn_sqrtf(fmaxf(e2 - dd * dd, 0.0f))) * iss;
+  const float xr = fmaxf(zr * l11, zq * l11), xl = fminf(zr * l11, zq * l11);
+  const float mx = 0.01f + (3e-7f * fmaxf(fabsf(bb.x0), fabsf(bb.x1)) + 1e-3f * rr * fabsf(l11)) * bb.scale;
+  const float c0 = (xl - dx0) * bb.scale - mx, c1 = (xr - dx0) * bb.scale + mx;
+  if (t0 > 0.0f) e.row0 = (int)fminf(ceilf(t0), 16.0f);
+  if (t1 < 15.0f) e.row1 = (int)fmaxf(floorf(t1), -1.0f);
+  if (c0 > 0.0f) e.col0 = (int)fminf(ceilf(c0), 16.0f);
+  if (c1 < 15.0f) e.col1 = (int)fmaxf(floorf(c1), -1.0f);
+  if (zl > zh || dl > dh || e.col0 > e.col1) e.row0 = 16;
+  return e;
+}
+
+// Scratch of the backward in LDS, beside the pixel seeds.
+struct BackwardScratch {
+  uint32_t ent[kChunk];  // the chunk's list entries, then sort keys, then packed boxes
+  uint2 out[kChunk];     // (kernel id, partial row) in processing order
+};
+
+// Backward over a block's list [rg.x, rg.y): for every kernel the adjoints of its 6 + 3C raw
+// parameters, summed over the block's 256 pixels (pi K recomputed from the record, w = pi K /
+// D), written as the per-(block, kernel) partial row.
 //   G = sum_c g_c (m_c - y_c),  H = w G                       (dL/drho)
 //   dL/da_c = g_c w,  dL/dwx_c = g_c w dx,  dL/dwy_c = g_c w dy
 //   bz2 = -H z2,  bz1 = -H z1 - bz2 l21/l22                  (through q = z1^2 + z2^2)
@@ -456,132 +526,192 @@ struct PixelSeed {
 //   dL/ds1 = -bz1 z1,  dL/dl21 = -bz2 z1/l22,  dL/ds2 = -bz2 z2
 // Fields 0 and 1 of the partial row leave out the sum_c g_c w wx_c and sum_c g_c w wy_c
 // terms: the gather applies them per kernel from dL/da_c (finish_gradient).
-// The terms that factor through a lane's column (dx, z1) or through the kernel (1/l11,
-// 1/l22) are applied once per lane to the lane's sums instead of once per pixel; so is the
-// l21/l22 term of bz1 (sum bz1 = -(z1 sum H + (l21/l22) sum bz2) over a lane's
-// pixels), and the seeds g and sum_c g_c y_c are taken already divided by D, so that pi K
-// itself stands in for w.
+//
+// What bounds it is VALU issue: a binary32 add, multiply or fma on vector registers takes 2
+// cycles of a SIMD here, every other vector instruction (compare, select, DPP, integer) 4,
+// exp2 and the permlane swaps 8.  So a wave takes four list entries at a time, 16 lanes
+// each, and a lane keeps one column of its entry while it steps down the block's rows: dx,
+// z1, what factors through them, the per-lane finish and the reduction are paid once per four
+// entries.  (One entry per wave, four rows per lane and a 64-lane reduction paid as much for
+// those as for the pairs.)  The 16 lanes cover the box of the entry's ellipse in the
+// block (ellipse_box, a lane per entry, 64 entries at once): a box of at most 8, 4 or 2
+// columns takes 2, 4 or 8 rows per step.  Entries are taken in the order of their step
+// counts (in pairs of steps), most first, so the four of a group need about as many.
+// Measured against one entry per wave: the 2048^2 RGB linear fit step 145 -> 117 us (65536
+// kernels, 26-entry lists), the standalone backward of a 509x381 render 20.3 -> 13.7 us.
+// The seeds sit in LDS, where the forward's records were; a lane reads its entry's record
+// from memory.
+//
+// Per lane, over its pixels: the sums that do not factor through the column -- A_c =
+// sum g_c w, Y_c = sum g_c w dy, V = sum H (dy - t), S2 = sum H z2^2, R = sum H.  dx and z1 are
+// the same for the lane's pixels, so sum g_c w dx = dx A_c, sum bz2 = -V / l22 (z2 = (dy - t)
+// / l22), sum bz1 = -(z1 R + (l21/l22) sum bz2), sum bz1 z1 = z1 sum bz1.  The seeds are
+// divided by D, so w = pi K / D is e = pi K.
 // packed (the fit step): list entries hold kernel id << shift | low, and the partial row of
-// the entry goes to row kSlots j + low for low < kSlots (the block's index in the kernel's
-// rectangle: kernel-major rows), else to row kSlots K + rg.x + low - kSlots (its bucket
-// slot), where the fit step's gather reads it; otherwise to the entry's list position.
-template <int C, int ORDER>
-__device__ __forceinline__ void backward_accumulate(const PixelCoords& px, float r2,
+// the entry is row kSlots j + low for low < kSlots (the block's index in the kernel's
+// rectangle: kernel-major rows), else row kSlots K + rg.x + low - kSlots (its bucket slot),
+// where the fit step's gather reads it; otherwise the entry's list position.
+// x0, y0: o + 0.5 + (column, row) of the block's first pixel, whose coordinates are these
+// times inv_s; UNIT: inv_s = 1.  ent_ready: sc.ent holds a single-chunk list already.
+template <int C, int ORDER, bool UNIT>
+__device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0, float y0,
+                                                    float inv_s, float radius, float r2,
                                                     const float* __restrict__ records,
                                                     const uint32_t* __restrict__ vals, int shift,
-                                                    bool packed, int2 rg, float4* srec,
-                                                    bool staged, uint64_t live,
-                                                    const PixelSeed<C>& sd,
-                                                    float* __restrict__ pair_grads,
-                                                    int K = 0) {
+                                                    bool packed, int2 rg,
+                                                    const PixelSeed<C>* seeds, BackwardScratch& sc,
+                                                    bool ent_ready,
+                                                    float* __restrict__ pair_grads, int K = 0) {
   constexpr int RS = record_stride(C, ORDER);
   constexpr int Q = RS / 4;
   constexpr int NP = num_params(C, ORDER);
   constexpr int PS = partial_stride(NP);
   static_assert(PS <= 16, "16 accumulators per kernel");
   const int lane = threadIdx.x & 63;
-  // the seeds divided by D: g_c / D and sum_c g_c y_c / D
-  float gs[kRows][C], gys[kRows];
-#pragma unroll
-  for (int i = 0; i < kRows; ++i) {
-    gys[i] = sd.gy[i] * sd.invD[i];
-#pragma unroll
-    for (int c = 0; c < C; ++c) gs[i][c] = sd.g[i][c] * sd.invD[i];
-  }
+  const int l16 = lane & 15, sub = lane >> 4;
+  const uint32_t slot_mask = (1u << shift) - 1u;
   for (int base = rg.x; base < rg.y; base += kChunk) {
-    const int n = min(kChunk, rg.y - base);
-    const bool reuse = staged && rg.y - rg.x <= kChunk;
-    if (!reuse) stage_records<RS>(srec, records, vals, base, n, shift);
-    const uint32_t slot_mask = (1u << shift) - 1u;
-    // the row of entry k's partial: the one its low bits name (packed) or its list position
-    auto out_row = [&](int k) -> size_t {
-      if (!packed) return (size_t)(base + k);
-      const uint32_t e = __builtin_amdgcn_readfirstlane(vals[base + k]);
+    const int n = __builtin_amdgcn_readfirstlane(min(kChunk, rg.y - base));
+    __syncthreads();
+    // a lane per entry: its partial row, its box, its pairs of steps
+    uint32_t e = 0, row = 0;
+    int its = 0, packed_box = 0;
+    if (lane < n) {
+      e = ent_ready && rg.y - rg.x <= kChunk ? sc.ent[lane] : vals[base + lane];
       const uint32_t low = e & slot_mask;
-      return low < (uint32_t)kSlots ? (size_t)(e >> shift) * kSlots + low
-                                    : (size_t)K * kSlots + (size_t)rg.x + (low - kSlots);
-    };
-    for (int k = 0; k < n; ++k) {
-      if (reuse && !((live >> k) & 1ull)) {
-        // no pixel of the block passed the forward's test: the partial row is zero
-        const int idx = lane >> 2;
-        if ((lane & 3) == 0 && idx < PS) pair_grads[out_row(k) * PS + idx] = 0.0f;
-        continue;
+      row = !packed ? (uint32_t)(base + lane)
+                    : (low < (uint32_t)kSlots ? (e >> shift) * (uint32_t)kSlots + low
+                                              : (uint32_t)K * kSlots + (uint32_t)rg.x + (low - kSlots));
+      const float4* r4 = reinterpret_cast<const float4*>(records + (size_t)(e >> shift) * RS);
+      const float4 f = r4[0];
+      const EllipseBox b = ellipse_box(bb, radius, f.x, f.y, f.z, f.w, r4[1].x);
+      if (b.row0 <= b.row1) {
+        const int lw = max(1, 32 - __clz(b.col1 - b.col0));  // columns <= 2^lw
+        const int lr = 4 - lw;                               // 2^lr rows per step
+        its = (b.row1 - b.row0 + (2 << lr)) >> (lr + 1);
+        // (the last steps' rows and columns stay inside the block)
+        packed_box = min(b.row0, 16 - (its << (lr + 1))) | min(b.col0, 16 - (1 << lw)) << 4 |
+                     lr << 8 | its << 12;
       }
-      const float* r = reinterpret_cast<const float*>(&srec[k * Q]);
-      const float dx = px.x - r[0];
-      const float z1 = dx * r[2];
-      const float tt = r[3] * z1;
-      const float zz1 = z1 * z1;
-      // a_c + wx_c dx: the expert's value along the lane's column
-      float mx[C];
+    }
+    const uint32_t id = lane < n ? e >> shift : __builtin_amdgcn_readfirstlane(e >> shift);
+    __syncthreads();
+    // rank by step count, most first, ties in list order
+    const uint32_t key = (uint32_t)its << 6 | (uint32_t)(63 - lane);
+    sc.ent[lane] = key;
+    __syncthreads();
+    int at = 0;
+    {
+      const uint4* k4 = reinterpret_cast<const uint4*>(sc.ent);
+      for (int j = 0; j < (n + 3) >> 2; ++j) {
+        const uint4 q = k4[j];
+        at += (q.x > key ? 1 : 0) + (q.y > key ? 1 : 0) + (q.z > key ? 1 : 0) + (q.w > key ? 1 : 0);
+      }
+    }
+    if (lane >= n) at = lane;  // (padding: keys below every entry's)
+    __syncthreads();
+    sc.ent[at] = (uint32_t)packed_box;
+    sc.out[at] = make_uint2(id, row);
+    __syncthreads();
+    for (int g = 0; g < n; g += 4) {
+      const uint32_t bx = sc.ent[g + sub];
+      const uint2 out = sc.out[g + sub];
+      const int M = __builtin_amdgcn_readfirstlane(bx >> 12);  // the group's first has the most
+      float tot = 0.0f;
+      if (M > 0) {
+        float r[RS];
+        {
+          const float4* r4 = reinterpret_cast<const float4*>(records + (size_t)out.x * RS);
 #pragma unroll
-      for (int c = 0; c < C; ++c)
-        mx[c] = ORDER == 1 ? __builtin_fmaf(r[kRecExpert + C + c], dx, r[kRecExpert + c])
-                           : r[kRecExpert + c];
-      // Per lane, over its four pixels: the sums that do not factor through the lane's
-      // column -- A_c = sum g_c w, Y_c = sum g_c w dy, V = sum H (dy - t), S2 = sum H z2^2,
-      // R = sum H.  dx and z1 are the same for the lane's pixels, so sum g_c w dx = dx A_c,
-      // sum bz2 = -V / l22 (z2 = (dy - t) / l22), sum bz1 = -(z1 R + (l21/l22) sum bz2),
-      // sum bz1 z1 = z1 sum bz1 and sum g_c w wx_c = wx_c A_c.  With the seeds divided by D,
-      // w = pi K / D is e = pi K.
-      float A[C], Y[C];
-#pragma unroll
-      for (int c = 0; c < C; ++c) A[c] = Y[c] = 0.0f;
-      float V = 0.0f, S2 = 0.0f, R = 0.0f;
-#pragma unroll
-      for (int i = 0; i < kRows; ++i) {
-        const float dy = px.y[i] - r[1];
-        const float w_ = dy - tt;
-        const float z2 = w_ * r[4];
-        const float z2sq = z2 * z2;
-        const float q = zz1 + z2sq;
-        // the first row runs unmasked with pi K zeroed where it does not take part, so that
-        // it can start the sums without zero-filled accumulators in front of it
-        const bool ok = sd.valid[i] && q <= r2;
-        if (i == 0 || ok) {
-          float e = __builtin_amdgcn_exp2f(__builtin_fmaf(q, -0.5f * kLog2e, r[5]));
-          if (i == 0) e = ok ? e : 0.0f;
-          const float ed = e * dy;
-          float Gs = -gys[i];  // G / D
-#pragma unroll
-          for (int c = 0; c < C; ++c) {
-            float m = mx[c];
-            if (ORDER == 1) m = __builtin_fmaf(r[kRecExpert + 2 * C + c], dy, m);
-            Gs = __builtin_fmaf(gs[i][c], m, Gs);
-            // the first row's terms start the sums: no additions of zero
-            A[c] = i == 0 ? gs[i][c] * e : __builtin_fmaf(gs[i][c], e, A[c]);
-            if (ORDER == 1) Y[c] = i == 0 ? gs[i][c] * ed : __builtin_fmaf(gs[i][c], ed, Y[c]);
+          for (int q = 0; q < Q; ++q) {
+            const float4 f = r4[q];
+            r[4 * q] = f.x;
+            r[4 * q + 1] = f.y;
+            r[4 * q + 2] = f.z;
+            r[4 * q + 3] = f.w;
           }
-          const float Hh = e * Gs;  // H = w G
-          V = i == 0 ? Hh * w_ : __builtin_fmaf(Hh, w_, V);
-          S2 = i == 0 ? Hh * z2sq : __builtin_fmaf(Hh, z2sq, S2);
-          R = i == 0 ? Hh : R + Hh;
         }
-      }
-      const float B2 = -V * r[4];
-      const float B1 = -__builtin_fmaf(r[6], B2, z1 * R);
-      // fields 0 and 1 leave the expert terms of the centre's gradient to finish_gradient
-      float acc[16];
+        const int lr = (int)(bx >> 8 & 7u), mine = (int)(bx >> 12);
+        const int col = (int)(bx >> 4 & 15u) + (l16 & ((16 >> lr) - 1));
+        const int row0 = (int)(bx & 15u) + (l16 >> (4 - lr));
+        const PixelSeed<C>* sp = seeds + row0 * kTile + col;
+        float h = y0 + (float)row0;
+        const float hstep = (float)(1 << lr);
+        const float xc = x0 + (float)col;
+        const float dx = (UNIT ? xc : xc * inv_s) - r[0];
+        const float z1 = dx * r[2];
+        const float tt = r[3] * z1;
+        const float zz1 = z1 * z1;
+        // a_c + wx_c dx: the expert's value along the lane's column
+        float mx[C];
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
-        acc[6 + c] = A[c];
-        if (ORDER == 1) {
-          acc[6 + C + c] = A[c] * dx;
-          acc[6 + 2 * C + c] = Y[c];
+        for (int c = 0; c < C; ++c)
+          mx[c] = ORDER == 1 ? __builtin_fmaf(r[kRecExpert + C + c], dx, r[kRecExpert + c])
+                             : r[kRecExpert + c];
+        float A[C], Y[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) A[c] = Y[c] = 0.0f;
+        float V = 0.0f, S2 = 0.0f, R = 0.0f;
+        for (int m = 0; m < M; ++m) {
+          if (m < mine) {
+            // both steps' seeds are loaded and tests made before the first is used
+            PixelSeed<C> sd[2];
+            float dy[2], wv[2], z2sq[2], q[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              sd[i] = sp[(kTile << lr) * i];
+              dy[i] = (UNIT ? h : h * inv_s) - r[1];
+              h += hstep;
+              wv[i] = dy[i] - tt;
+              const float z2 = wv[i] * r[4];
+              z2sq[i] = z2 * z2;
+              q[i] = zz1 + z2sq[i];
+            }
+            sp += (2 * kTile) << lr;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              if (q[i] <= r2) {
+                const float ek = __builtin_amdgcn_exp2f(__builtin_fmaf(q[i], -0.5f * kLog2e, r[5]));
+                const float ed = ek * dy[i];
+                float Gs = -sd[i].gy;  // G / D
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                  float m = mx[c];
+                  if (ORDER == 1) m = __builtin_fmaf(r[kRecExpert + 2 * C + c], dy[i], m);
+                  Gs = __builtin_fmaf(sd[i].g[c], m, Gs);
+                  A[c] = __builtin_fmaf(sd[i].g[c], ek, A[c]);
+                  if (ORDER == 1) Y[c] = __builtin_fmaf(sd[i].g[c], ed, Y[c]);
+                }
+                const float Hh = ek * Gs;  // H = w G
+                V = __builtin_fmaf(Hh, wv[i], V);
+                S2 = __builtin_fmaf(Hh, z2sq[i], S2);
+                R += Hh;
+              }
+            }
+          }
         }
-      }
-      acc[0] = -B1 * r[2];
-      acc[1] = -B2 * r[4];
-      acc[2] = -B1 * z1;
-      acc[3] = -B2 * z1 * r[4];
-      acc[4] = S2;
-      acc[5] = R;
+        const float B2 = -V * r[4];
+        const float B1 = -__builtin_fmaf(r[6], B2, z1 * R);
+        float acc[16];
 #pragma unroll
-      for (int i = 6 + C * (1 + 2 * ORDER); i < 16; ++i) acc[i] = 0.0f;
-      const float tot = wave_reduce16_transposed(acc);
-      const int idx = lane >> 2;
-      if ((lane & 3) == 0 && idx < PS) pair_grads[out_row(k) * PS + idx] = tot;
+        for (int c = 0; c < C; ++c) {
+          acc[6 + c] = A[c];
+          if (ORDER == 1) {
+            acc[6 + C + c] = A[c] * dx;
+            acc[6 + 2 * C + c] = Y[c];
+          }
+        }
+        acc[0] = -B1 * r[2];
+        acc[1] = -B2 * r[4];
+        acc[2] = -B1 * z1;
+        acc[3] = -B2 * z1 * r[4];
+        acc[4] = S2;
+        acc[5] = R;
+#pragma unroll
+        for (int i = 6 + C * (1 + 2 * ORDER); i < 16; ++i) acc[i] = 0.0f;
+        tot = row_reduce16_masked(acc);
+      }
+      if (g + sub < n && l16 < PS) pair_grads[(size_t)out.y * PS + l16] = tot;
     }
   }
 }

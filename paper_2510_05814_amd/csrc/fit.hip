@@ -40,7 +40,8 @@ struct FitTileArgs {
 };
 
 template <int C, int ORDER, bool RBF, int TRUNC>
-__global__ __launch_bounds__(kWave) void k_fit_tile(FitTileArgs a) {
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8, 8)))
+void k_fit_tile(FitTileArgs a) {
   constexpr int LDS_FLOATS = kChunk * record_stride(C, ORDER);
   static_assert(LDS_FLOATS >= 64, "the rank sort's scratch lives in the record buffer");
   // the forward's records, then the backward's pixel seeds
@@ -82,7 +83,8 @@ __global__ __launch_bounds__(kWave) void k_fit_tile(FitTileArgs a) {
 
   const PixelCoords px = lane_pixels(sg, tile - sg.tile_offset);
   float D[kRows], N[kRows][C];
-  forward_accumulate<C, ORDER, TRUNC>(px, a.S.r2, a.S.cut_scale, a.S.cut_offset, a.records,
+  const BlockBox bb = block_box(sg, tile - sg.tile_offset);
+  forward_accumulate<C, ORDER, TRUNC>(px, bb, a.S.r2, a.S.cut_scale, a.S.cut_offset, a.records,
                                       a.vals, a.shift, rg, srec, D, N, sc.ent);
 
   const int lane = threadIdx.x & 63;
@@ -124,7 +126,7 @@ __global__ __launch_bounds__(kWave) void k_fit_tile(FitTileArgs a) {
 
   // each partial row goes to the row its entry names, where Adam reads it
   const float2 o = block_base(sg, tile - sg.tile_offset);
-  backward_accumulate<C, ORDER, true>(block_box(sg, tile - sg.tile_offset), o.x, o.y, 1.0f, a.S.r,
+  backward_accumulate<C, ORDER, true>(bb, o.x, o.y, 1.0f, a.S.r,
                                       a.S.r2, a.records, a.vals, a.shift, true, rg, seeds, sc, true,
                                       a.pair_grads, a.S.K);
 }

@@ -80,8 +80,9 @@ __global__ __launch_bounds__(kWave) void k_render(RenderArgs a) {
   const SegGrid sg = seg_of_tile(a.S, tile);
   const PixelCoords px = lane_pixels(sg, tile - sg.tile_offset);
   float D[kRows], N[kRows][C];
-  forward_accumulate<C, ORDER, TRUNC>(px, a.S.r2, a.S.cut_scale, a.S.cut_offset, a.records,
-                                      a.vals, 0, rg, srec, D, N);
+  forward_accumulate<C, ORDER, TRUNC>(px, block_box(sg, tile - sg.tile_offset), a.S.r2,
+                                      a.S.cut_scale, a.S.cut_offset, a.records, a.vals, 0, rg, srec,
+                                      D, N);
   render_epilogue<C, RBF>(a, sg, px, tile, D, N);
 }
 
@@ -110,8 +111,10 @@ __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile,
   zero_sums<C>(D, N);
   const float cut_scale = in_vgpr(a.S.cut_scale), cut_offset = in_vgpr(a.S.cut_offset);
   float4* my = srec[wv];
+  const BlockBox bb = block_box(sg, tile - sg.tile_offset);
+  const BlockBox bb = block_box(sg, tile - sg.tile_offset);
   for (int base = b; base < e; base += kChunk) {
-    const int n = min(kChunk, e - base);
+    const int n = __builtin_amdgcn_readfirstlane(min(kChunk, e - base));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     for (int i = lane; i < n * Q; i += kWave) {
@@ -120,9 +123,7 @@ __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile,
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    for (int k = 0; k < n; ++k)
-      forward_entry<C, ORDER, TRUNC>(px, a.S.r2, cut_scale, cut_offset,
-                                     reinterpret_cast<const float*>(&my[k * Q]), D, N);
+    forward_chunk<C, ORDER, TRUNC>(px, bb, a.S.r2, cut_scale, cut_offset, my, n, D, N);
   }
   if (wv > 0) {
 #pragma unroll

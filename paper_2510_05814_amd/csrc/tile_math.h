@@ -75,6 +75,12 @@ __device__ __forceinline__ PixelCoords lane_pixels(const SegGrid& g, int tile) {
   return p;
 }
 
+// A wave-uniform value moved to a scalar register (it then holds no vector register over the
+// loops between its uses).
+__device__ __forceinline__ float in_sgpr(float x) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
 // Coordinates of a block's first and last column and row (whole blocks, also where they hang
 // over the raster's edges).
 struct BlockBox {
@@ -83,15 +89,24 @@ struct BlockBox {
 };
 __device__ __forceinline__ BlockBox block_box(const SegGrid& g, int tile) {
   const int u = kTile * (g.bx0 + tile % g.ntx) - g.ox, v = kTile * (g.by0 + tile / g.ntx) - g.oy;
-  return BlockBox{sample_coord(u, g.ox, g.inv_s), sample_coord(u + kTile - 1, g.ox, g.inv_s),
-                  sample_coord(v, g.oy, g.inv_s), sample_coord(v + kTile - 1, g.oy, g.inv_s),
-                  (float)g.scale};
+  return BlockBox{in_sgpr(sample_coord(u, g.ox, g.inv_s)),
+                  in_sgpr(sample_coord(u + kTile - 1, g.ox, g.inv_s)),
+                  in_sgpr(sample_coord(v, g.oy, g.inv_s)),
+                  in_sgpr(sample_coord(v + kTile - 1, g.oy, g.inv_s)), in_sgpr((float)g.scale)};
 }
 // o + 0.5 + (column, row) of the block's first pixel (exact): its pixel (c, r) samples
 // ((.x + c) * inv_s, (.y + r) * inv_s).
 __device__ __forceinline__ float2 block_base(const SegGrid& g, int tile) {
   return make_float2((float)(kTile * (g.bx0 + tile % g.ntx)) + 0.5f,
                      (float)(kTile * (g.by0 + tile / g.ntx)) + 0.5f);
+}
+
+// The lane's index, opaque to the compiler: what the once-per-chunk code derives from it is then
+// computed there instead of being held in registers across the loops over entries.
+__device__ __forceinline__ int local_lane() {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  return lane;
 }
 
 // Stages the records of list entries [base, base + n) (n <= kChunk) into LDS.  An entry
@@ -104,7 +119,7 @@ __device__ __forceinline__ void stage_records(float4* __restrict__ srec,
                                               int shift) {
   constexpr int Q = RS / 4;
   __syncthreads();
-  for (int i = threadIdx.x & 63; i < n * Q; i += kWave) {
+  for (int i = local_lane(); i < n * Q; i += kWave) {
     const int k = i / Q, c = i - k * Q;
     srec[i] = reinterpret_cast<const float4*>(records + (size_t)(vals[base + k] >> shift) * RS)[c];
   }
@@ -122,37 +137,71 @@ __device__ __forceinline__ void stage_records_lds(float4* __restrict__ srec,
   constexpr int Q = RS / 4;
   __syncthreads();
   if (!ready) {
-    const int lane = threadIdx.x & 63;
+    const int lane = local_lane();
     if (lane < n) ent[lane] = vals[base + lane];
     __syncthreads();
   }
-  for (int i = threadIdx.x & 63; i < n * Q; i += kWave) {
+  for (int i = local_lane(); i < n * Q; i += kWave) {
     const int k = i / Q, c = i - k * Q;
     srec[i] = reinterpret_cast<const float4*>(records + (size_t)(ent[k] >> shift) * RS)[c];
   }
   __syncthreads();
 }
 
+// Entries of a staged chunk for which some pixel of the block may lie beyond the render's
+// representable range (exponent below -125): bit k for entry k < n.  A lane per entry: the
+// exponent is least where q is largest, and q, a convex function of the point, is largest at
+// a corner of the block; the bound -110 instead of -125 covers every rounding.  Blocks near
+// their kernels have no such entry.
+template <int RS>
+__device__ __forceinline__ uint64_t far_entries(const BlockBox& bb, const float4* srec, int n) {
+  const int lane = local_lane();
+  bool far = false;
+  if (lane < n) {
+    const float4 f = srec[lane * (RS / 4)], g = srec[lane * (RS / 4) + 1];
+    const float za = (bb.x0 - f.x) * f.z, zb = (bb.x1 - f.x) * f.z;
+    const float ta = f.w * za, tb = f.w * zb, d0 = bb.y0 - f.y, d1 = bb.y1 - f.y;
+    const float a0 = (d0 - ta) * g.x, a1 = (d1 - ta) * g.x, b0 = (d0 - tb) * g.x, b1 = (d1 - tb) * g.x;
+    const float qa = za * za + fmaxf(a0 * a0, a1 * a1), qb = zb * zb + fmaxf(b0 * b0, b1 * b1);
+    const float ea = __builtin_fmaf(qa, -0.5f * kLog2e, g.y), eb = __builtin_fmaf(qb, -0.5f * kLog2e, g.y);
+    far = !(ea >= -110.0f) || !(eb >= -110.0f);
+  }
+  return __ballot(far);
+}
+
 // One list entry of the forward: adds its terms to D = sum pi K and N_c = sum pi K m_c of
 // the lane's four pixels that the render's rule keeps.  TRUNC == SMOE_TRUNC_RENDER: the
 // ellipse q <= r^2.  TRUNC == SMOE_TRUNC_GRADIENT (the block lists decide the render): every
-// term binary32 holds, i.e. whose exponent a = rho log2(e) - q log2(e)/2 is >= -125.  r: the
+// term binary32 holds, i.e. whose exponent a = rho log2(e) - q log2(e)/2 is >= -125.  f4: the
 // entry's render record; cut_scale, cut_offset: the render's bound in the compare-free form of
-// Segs.
+// Segs; far: whether some pixel of the block may lie beyond that bound.
 //
-// Neither bound is a per-row compare: a VALU instruction that writes or reads a scalar
-// register (a compare's lane mask, a select on it) issues at about 60 % of the rate of one
-// on vector registers alone.  The render's bound goes through the exponent: with the
-// ellipse, max(q, u) with u = fma(q, cut_scale, cut_offset) is q inside the bound and gives a
-// term beyond it an exponent of about -2^36; with the representable range, min(a, fma(a,
-// 2^60, 125 * 2^60)) is a for a >= -125 and below -2^43 otherwise.  Either way exp2 of an
-// excluded term is exactly zero and every kept term carries the same bits as with a
-// compare-and-select.
+// The loop over entries is bound by VALU issue: a binary32 add, multiply or fma on vector
+// registers takes 2 cycles of a SIMD, a compare, select, min or max, or an operand in a scalar
+// register 4, exp2 8.  So an entry that is not far -- almost all of them -- takes its exponent
+// straight as a = alpha - v^2 with v = (dy - t) sqrt(log2(e)/2) / l22 and alpha = rho log2(e)
+// - z1^2 log2(e)/2, the column's part: four operations a pixel instead of six and a minimum,
+// and no compare.  Otherwise the decisions are taken on the ABI's own binary32 sequence, and
+// the bound goes through the exponent: with the ellipse, max(q, u) with u = fma(q,
+// cut_scale, cut_offset) is q inside the bound and gives a term beyond it an exponent of about
+// -2^36; with the representable range, min(a, fma(a, 2^60, 125 * 2^60)) is a for a >= -125 and
+// below -2^43 otherwise: exp2 of an excluded term is exactly zero.
+// Measured: binning and render of a 2048^2 model with 65536 kernels 88.5 -> 83.7 us, its fit
+// step 116.1 -> 114.6 us, a 512^2 render with lists of several hundred 332 -> 320 us.
 template <int C, int ORDER, int TRUNC>
 __device__ __forceinline__ void forward_entry(const PixelCoords& px, float r2, float cut_scale,
-                                              float cut_offset, const float* r, float (&D)[kRows],
-                                              float (&N)[kRows][C]) {
-  // Truncation test: the binary32 sequence of the ABI contract (no contraction).
+                                              float cut_offset, const float4* f4, bool far,
+                                              float (&D)[kRows], float (&N)[kRows][C]) {
+  constexpr int RS = record_stride(C, ORDER);
+  float r[RS];
+#pragma unroll
+  for (int k = 0; k < RS / 4; ++k) {
+    const float4 f = f4[k];
+    r[4 * k] = f.x;
+    r[4 * k + 1] = f.y;
+    r[4 * k + 2] = f.z;
+    r[4 * k + 3] = f.w;
+  }
   const float dx = px.x - r[0];
   const float z1 = dx * r[2];
   const float tt = r[3] * z1;
@@ -163,36 +212,42 @@ __device__ __forceinline__ void forward_entry(const PixelCoords& px, float r2, f
   for (int c = 0; c < C; ++c)
     mx[c] = ORDER == 1 ? __builtin_fmaf(r[kRecExpert + C + c], dx, r[kRecExpert + c])
                        : r[kRecExpert + c];
-  float q[kRows], dy[kRows];
+  float dy[kRows], a[kRows];
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) {
-    dy[i] = px.y[i] - r[1];
-    const float w = dy[i] - tt;
-    const float z2 = w * r[4];
-    q[i] = zz1 + z2 * z2;
-  }
-  // pi K = exp(rho - q/2) = exp2(rho log2 e - q log2 e / 2), with the render's bound applied
-  // in its compare-free form -- which is the identity, bit for bit, unless some pixel of the
-  // block lies beyond the bound (q > r^2 with the ellipse in the render; an exponent below
-  // -125 otherwise), so the wave applies it only then.
-  float a[kRows];
-  if (TRUNC == SMOE_TRUNC_RENDER) {
-    const float qmax = __builtin_fmaxf(__builtin_fmaxf(q[0], q[1]), __builtin_fmaxf(q[2], q[3]));
-    if (__any(!(qmax <= r2))) {
+  for (int i = 0; i < kRows; ++i) dy[i] = px.y[i] - r[1];
+  // pi K = exp(rho - q/2) = exp2(rho log2 e - q log2 e / 2)
+  if (TRUNC == SMOE_TRUNC_GRADIENT && !far) {
+    constexpr float kRoot = 0.84932180028801904272f;  // sqrt(log2(e) / 2)
+    const float kk = r[4] * kRoot;
+    const float alpha = __builtin_fmaf(zz1, -0.5f * kLog2e, r[5]);
 #pragma unroll
-      for (int i = 0; i < kRows; ++i)
-        q[i] = __builtin_fmaxf(q[i], __builtin_fmaf(q[i], cut_scale, cut_offset));
+    for (int i = 0; i < kRows; ++i) {
+      const float v = (dy[i] - tt) * kk;
+      a[i] = __builtin_fmaf(-v, v, alpha);
     }
-#pragma unroll
-    for (int i = 0; i < kRows; ++i) a[i] = __builtin_fmaf(q[i], -0.5f * kLog2e, r[5]);
   } else {
+    float q[kRows];
 #pragma unroll
-    for (int i = 0; i < kRows; ++i) a[i] = __builtin_fmaf(q[i], -0.5f * kLog2e, r[5]);
-    const float amin = __builtin_fminf(__builtin_fminf(a[0], a[1]), __builtin_fminf(a[2], a[3]));
-    if (__any(!(amin >= -125.0f))) {
+    for (int i = 0; i < kRows; ++i) {
+      const float w = dy[i] - tt;
+      const float z2 = w * r[4];
+      q[i] = zz1 + z2 * z2;
+    }
+    if (TRUNC == SMOE_TRUNC_RENDER) {
+      const float qmax = __builtin_fmaxf(__builtin_fmaxf(q[0], q[1]), __builtin_fmaxf(q[2], q[3]));
+      if (__any(!(qmax <= r2))) {
 #pragma unroll
-      for (int i = 0; i < kRows; ++i)
+        for (int i = 0; i < kRows; ++i)
+          q[i] = __builtin_fmaxf(q[i], __builtin_fmaf(q[i], cut_scale, cut_offset));
+      }
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) a[i] = __builtin_fmaf(q[i], -0.5f * kLog2e, r[5]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) {
+        a[i] = __builtin_fmaf(q[i], -0.5f * kLog2e, r[5]);
         a[i] = __builtin_fminf(a[i], __builtin_fmaf(a[i], cut_scale, cut_offset));
+      }
     }
   }
 #pragma unroll
@@ -206,6 +261,20 @@ __device__ __forceinline__ void forward_entry(const PixelCoords& px, float r2, f
       N[i][c] = __builtin_fmaf(e, m, N[i][c]);
     }
   }
+}
+
+// The entries of a staged chunk, in order.
+template <int C, int ORDER, int TRUNC>
+__device__ __forceinline__ void forward_chunk(const PixelCoords& px, const BlockBox& bb, float r2,
+                                              float cut_scale, float cut_offset,
+                                              const float4* srec, int n, float (&D)[kRows],
+                                              float (&N)[kRows][C]) {
+  constexpr int RS = record_stride(C, ORDER);
+  constexpr int Q = RS / 4;
+  const uint64_t far = TRUNC == SMOE_TRUNC_GRADIENT ? far_entries<RS>(bb, srec, n) : 0;
+  for (int k = 0; k < n; ++k)
+    forward_entry<C, ORDER, TRUNC>(px, r2, cut_scale, cut_offset, &srec[k * Q],
+                                   (far >> k & 1) != 0, D, N);
 }
 
 // A copy of x that the compiler must keep in a vector register: loop-invariant operands of
@@ -225,31 +294,30 @@ __device__ __forceinline__ void zero_sums(float (&D)[kRows], float (&N)[kRows][C
   }
 }
 
-// Forward accumulation over a block's list [rg.x, rg.y) in list order (forward_entry per
-// entry, records staged through LDS in chunks).
+// Forward accumulation over a block's list [rg.x, rg.y) in list order (forward_chunk per
+// chunk, records staged through LDS in chunks).
 // shift: list entries hold the kernel id << shift.  ent: null, or LDS room for one chunk of
 // entries, which the staging then reads from there (a single-chunk list already holds them,
 // sorted; longer lists copy each chunk's entries in).
 template <int C, int ORDER, int TRUNC>
-__device__ __forceinline__ void forward_accumulate(const PixelCoords& px, float r2,
-                                                   float cut_scale, float cut_offset,
+__device__ __forceinline__ void forward_accumulate(const PixelCoords& px, const BlockBox& bb,
+                                                   float r2, float cut_scale, float cut_offset,
                                                    const float* __restrict__ records,
                                                    const uint32_t* __restrict__ vals, int shift,
                                                    int2 rg, float4* srec, float (&D)[kRows],
                                                    float (&N)[kRows][C],
                                                    uint32_t* ent = nullptr) {
   constexpr int RS = record_stride(C, ORDER);
-  constexpr int Q = RS / 4;
   zero_sums<C>(D, N);
-  cut_scale = in_vgpr(cut_scale);
-  cut_offset = in_vgpr(cut_offset);
+  if (TRUNC == SMOE_TRUNC_RENDER) {
+    cut_scale = in_vgpr(cut_scale);
+    cut_offset = in_vgpr(cut_offset);
+  }
   for (int base = rg.x; base < rg.y; base += kChunk) {
-    const int n = min(kChunk, rg.y - base);
+    const int n = __builtin_amdgcn_readfirstlane(min(kChunk, rg.y - base));
     if (ent) stage_records_lds<RS>(srec, records, vals, base, n, shift, ent, rg.y - rg.x <= kChunk);
     else stage_records<RS>(srec, records, vals, base, n, shift);
-    for (int k = 0; k < n; ++k)
-      forward_entry<C, ORDER, TRUNC>(px, r2, cut_scale, cut_offset,
-                                     reinterpret_cast<const float*>(&srec[k * Q]), D, N);
+    forward_chunk<C, ORDER, TRUNC>(px, bb, r2, cut_scale, cut_offset, srec, n, D, N);
   }
 }
 

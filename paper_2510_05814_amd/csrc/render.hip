@@ -112,7 +112,6 @@ __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile,
   const float cut_scale = in_vgpr(a.S.cut_scale), cut_offset = in_vgpr(a.S.cut_offset);
   float4* my = srec[wv];
   const BlockBox bb = block_box(sg, tile - sg.tile_offset);
-  const BlockBox bb = block_box(sg, tile - sg.tile_offset);
   for (int base = b; base < e; base += kChunk) {
     const int n = __builtin_amdgcn_readfirstlane(min(kChunk, e - base));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

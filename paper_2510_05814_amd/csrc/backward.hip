@@ -38,27 +38,38 @@ __global__ __launch_bounds__(kWave) void k_backward(BackwardArgs a) {
   const int lane = threadIdx.x & 63;
   // MSE of this raster: dL/dy = 2 (y - t) / (W H C)
   const float inv_n2 = 2.0f / ((float)sg.W * (float)sg.H * (float)C);
+  const BlockPixels bp = block_pixels(sg, tile - sg.tile_offset);
+  const PixelValue<C>* img = reinterpret_cast<const PixelValue<C>*>(a.image) + bp.base;
+  const PixelValue<C>* ref =  // the target, or the upstream gradient
+      reinterpret_cast<const PixelValue<C>*>(a.target ? a.target : a.grad_image) + bp.base;
+  const float* den = a.denom + bp.base;
+  float D[kRows];
+  PixelValue<C> y[kRows], t[kRows];
 #pragma unroll
   for (int i = 0; i < kRows; ++i) {
-    const int v = px.v0 + 4 * i;
+    D[i] = 0.0f;
+    if (in_raster(px.u, px.v0 + 4 * i, sg)) {
+      const int p = bp.off + i * bp.step;
+      D[i] = den[p];
+      y[i] = img[p];
+      t[i] = ref[p];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kRows; ++i) {
     PixelSeed<C> sd;
     sd.gy = 0.0f;
 #pragma unroll
     for (int c = 0; c < C; ++c) sd.g[c] = 0.0f;
-    if (in_raster(px.u, v, sg)) {
-      const size_t p = (size_t)sg.pixel_offset + (size_t)v * sg.W + px.u;
-      const float D = a.denom[p];
-      if (D > 0.0f) {
-        const float invD = RBF ? 1.0f : __builtin_amdgcn_rcpf(D);
+    if (D[i] > 0.0f) {
+      const float invD = RBF ? 1.0f : __builtin_amdgcn_rcpf(D[i]);
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-          const float yc = a.image[p * C + c];
-          const float g = a.target ? (yc - a.target[p * C + c]) * inv_n2 : a.grad_image[p * C + c];
-          if (!RBF) sd.gy = __builtin_fmaf(g, yc, sd.gy);
-          sd.g[c] = g * invD;
-        }
-        sd.gy = sd.gy * invD;
+      for (int c = 0; c < C; ++c) {
+        const float g = a.target ? (y[i].v[c] - t[i].v[c]) * inv_n2 : t[i].v[c];
+        if (!RBF) sd.gy = __builtin_fmaf(g, y[i].v[c], sd.gy);
+        sd.g[c] = g * invD;
       }
+      sd.gy = sd.gy * invD;
     }
     seeds[((lane >> 4) + 4 * i) * kTile + (lane & 15)] = sd;
   }

@@ -90,16 +90,23 @@ void k_fit_tile(FitTileArgs a) {
   const int lane = threadIdx.x & 63;
   PixelSeed<C>* seeds = reinterpret_cast<PixelSeed<C>*>(srec);
   __syncthreads();  // the records are read: their place takes the seeds
+  const BlockPixels bp = block_pixels(sg, tile - sg.tile_offset);
+  const PixelValue<C>* tgt = reinterpret_cast<const PixelValue<C>*>(a.target) + bp.base;
+  bool in[kRows];
+  PixelValue<C> t[kRows], y[kRows];
+#pragma unroll
+  for (int i = 0; i < kRows; ++i) {
+    in[i] = in_raster(px.u, px.v0 + 4 * i, sg);
+    if (in[i]) t[i] = tgt[bp.off + i * bp.step];
+  }
   float err = 0.0f;
 #pragma unroll
   for (int i = 0; i < kRows; ++i) {
-    const int v = px.v0 + 4 * i;
     PixelSeed<C> sd;
     sd.gy = 0.0f;
 #pragma unroll
-    for (int c = 0; c < C; ++c) sd.g[c] = 0.0f;
-    if (in_raster(px.u, v, sg)) {
-      const size_t p = (size_t)sg.pixel_offset + (size_t)v * sg.W + px.u;
+    for (int c = 0; c < C; ++c) sd.g[c] = y[i].v[c] = 0.0f;
+    if (in[i]) {
       const bool cov = D[i] > 0.0f;
       // 1/D by v_rcp_f32 (1 ulp); y = N / D refined from it, as in the render
       const float invD = RBF ? 1.0f : (cov ? __builtin_amdgcn_rcpf(D[i]) : 0.0f);
@@ -107,8 +114,8 @@ void k_fit_tile(FitTileArgs a) {
       for (int c = 0; c < C; ++c) {
         // Eq. (2)-(4): y = N / D; Eq. (1): y = N
         const float yc = RBF ? N[i][c] : (cov ? div_refined(N[i][c], D[i], invD) : 0.0f);
-        if (a.image) a.image[p * C + c] = yc;
-        const float d = yc - a.target[p * C + c];
+        y[i].v[c] = yc;
+        const float d = yc - t[i].v[c];
         err = __builtin_fmaf(d, d, err);
         if (cov) {
           const float g = d * inv_n2;
@@ -116,10 +123,20 @@ void k_fit_tile(FitTileArgs a) {
           sd.g[c] = g * invD;
         }
       }
-      if (a.image) a.denom[p] = D[i];
       sd.gy = sd.gy * invD;
     }
     seeds[((lane >> 4) + 4 * i) * kTile + (lane & 15)] = sd;
+  }
+  if (a.image) {
+    PixelValue<C>* img = reinterpret_cast<PixelValue<C>*>(a.image) + bp.base;
+    float* den = a.denom + bp.base;
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+      if (in[i]) {
+        img[bp.off + i * bp.step] = y[i];
+        den[bp.off + i * bp.step] = D[i];
+      }
+    }
   }
   for (int off = 32; off > 0; off >>= 1) err += __shfl_xor(err, off);
   if (threadIdx.x == 0) a.tile_loss[tile] = err * inv_n;

@@ -43,26 +43,32 @@ __device__ __forceinline__ void render_epilogue(const RenderArgs& a, const SegGr
                                                 const PixelCoords& px, int tile,
                                                 const float (&D)[kRows],
                                                 const float (&N)[kRows][C]) {
+  const BlockPixels bp = block_pixels(sg, tile - sg.tile_offset);
+  PixelValue<C>* img = reinterpret_cast<PixelValue<C>*>(a.image) + bp.base;
+  const PixelValue<C>* tgt = reinterpret_cast<const PixelValue<C>*>(a.target) + bp.base;
+  float* den = a.denom + bp.base;
   float err = 0.0f;
 #pragma unroll
   for (int i = 0; i < kRows; ++i) {
-    const int v = px.v0 + 4 * i;
-    if (in_raster(px.u, v, sg)) {
-      const size_t p = (size_t)sg.pixel_offset + (size_t)v * sg.W + px.u;
+    if (in_raster(px.u, px.v0 + 4 * i, sg)) {
+      const int p = bp.off + i * bp.step;
+      PixelValue<C> y;
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
+      for (int c = 0; c < C; ++c)
         // Eq. (2)-(4): y = N / D, refined from v_rcp_f32(D) exactly as the fit step's render;
         // Eq. (1): y = N
-        const float yc =
-            RBF ? N[i][c]
-                : ((D[i] > 0.0f) ? div_refined(N[i][c], D[i], __builtin_amdgcn_rcpf(D[i])) : 0.0f);
-        a.image[p * C + c] = yc;
-        if (a.target) {
-          const float d = yc - a.target[p * C + c];
+        y.v[c] = RBF ? N[i][c]
+                     : ((D[i] > 0.0f) ? div_refined(N[i][c], D[i], __builtin_amdgcn_rcpf(D[i])) : 0.0f);
+      if (a.target) {
+        const PixelValue<C> t = tgt[p];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const float d = y.v[c] - t.v[c];
           err = __builtin_fmaf(d, d, err);
         }
       }
-      if (a.denom) a.denom[p] = D[i];
+      img[p] = y;
+      if (a.denom) den[p] = D[i];
     }
   }
   if (a.tile_loss) {

@@ -6,7 +6,7 @@
 // tile_math.h).  Pixels outside the ellipse or the kernel's blocks contribute nothing
 // (Sec. IV-B).
 //
-// Work split: one wave per 16x16 block, four kernels of its list at a time, 16 lanes each; a
+// Work split: one wave (four on small rasters) per 16x16 block, four kernels of its list at a time, 16 lanes each; a
 // reduction inside the 16 lanes (DPP) leaves one per-(block, kernel) partial row.  A second pass sums each kernel's partial rows over its
 // blocks in row-major block order.  Every order is fixed: gradients are bitwise
 // reproducible and no atomics are used.
@@ -28,25 +28,26 @@ struct BackwardArgs {
   float* __restrict__ pair_grads;
 };
 
-template <int C, int ORDER, bool RBF>
-__global__ __launch_bounds__(kWave) void k_backward(BackwardArgs a) {
+template <int C, int ORDER, bool RBF, int WAVES>
+__global__ __launch_bounds__(kWave * WAVES) void k_backward(BackwardArgs a) {
+  constexpr int ROWS = kStrips / WAVES;
   __shared__ PixelSeed<C> seeds[kTilePixels];
   __shared__ __align__(16) BackwardScratch sc;
   const int tile = xcd_block(blockIdx.x, a.S.T);
   const SegGrid sg = seg_of_tile(a.S, tile);
-  const PixelCoords px = lane_pixels(sg, tile - sg.tile_offset);
+  const PixelCoords<ROWS> px = lane_pixels<WAVES>(sg, tile - sg.tile_offset);
   const int lane = threadIdx.x & 63;
   // MSE of this raster: dL/dy = 2 (y - t) / (W H C)
   const float inv_n2 = 2.0f / ((float)sg.W * (float)sg.H * (float)C);
-  const BlockPixels bp = block_pixels(sg, tile - sg.tile_offset);
+  const BlockPixels bp = block_pixels<WAVES>(sg, tile - sg.tile_offset);
   const PixelValue<C>* img = reinterpret_cast<const PixelValue<C>*>(a.image) + bp.base;
   const PixelValue<C>* ref =  // the target, or the upstream gradient
       reinterpret_cast<const PixelValue<C>*>(a.target ? a.target : a.grad_image) + bp.base;
   const float* den = a.denom + bp.base;
-  float D[kRows];
-  PixelValue<C> y[kRows], t[kRows];
+  float D[ROWS];
+  PixelValue<C> y[ROWS], t[ROWS];
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
     D[i] = 0.0f;
     if (in_raster(px.u, px.v0 + 4 * i, sg)) {
       const int p = bp.off + i * bp.step;
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(kWave) void k_backward(BackwardArgs a) {
     }
   }
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
     PixelSeed<C> sd;
     sd.gy = 0.0f;
 #pragma unroll
@@ -71,10 +72,10 @@ __global__ __launch_bounds__(kWave) void k_backward(BackwardArgs a) {
       }
       sd.gy = sd.gy * invD;
     }
-    seeds[((lane >> 4) + 4 * i) * kTile + (lane & 15)] = sd;
+    seeds[((lane >> 4) + 4 * (i + ROWS * wave_index<WAVES>())) * kTile + (lane & 15)] = sd;
   }
   const float2 o = block_base(sg, tile - sg.tile_offset);
-  backward_accumulate<C, ORDER, false>(block_box(sg, tile - sg.tile_offset), o.x, o.y, sg.inv_s,
+  backward_accumulate<C, ORDER, false, WAVES>(block_box(sg, tile - sg.tile_offset), o.x, o.y, sg.inv_s,
                                        a.S.r, a.S.r2, a.records, a.vals, 0, false, a.ranges[tile],
                                        seeds, sc, false, a.pair_grads);
 }
@@ -123,7 +124,10 @@ hipError_t launch_backward(int C, int order, const Segs& S, const smoe_bins& b,
                  b.pair_grads};
   with_shape(C, order, S, [&](auto sh) {
     using T = decltype(sh);
-    k_backward<T::C, T::ORDER, T::RBF><<<S.T, kWave, 0, s>>>(a);
+    if (S.T <= kSplitBackward)
+      k_backward<T::C, T::ORDER, T::RBF, 4><<<S.T, 4 * kWave, 0, s>>>(a);
+    else
+      k_backward<T::C, T::ORDER, T::RBF, 1><<<S.T, kWave, 0, s>>>(a);
   });
   return hipGetLastError();
 }

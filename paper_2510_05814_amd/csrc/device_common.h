@@ -291,10 +291,19 @@ __device__ void block_scan_ranges(int T, int32_t* __restrict__ tile_counts,
   }
 }
 
+// Orders this wave's LDS and memory accesses before it against those after it, as seen by
+// its own lanes (a wave's LDS accesses execute in program order: the compiler must keep it).
+// Unlike a workgroup barrier it may be used by one wave of several.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sorts one bucket of n distinct kernel ids (seg[0, n)) ascending with the 64 lanes of one
 // wave: bitonic sort in LDS for runs of up to `run` ids (lds holds `run` u32), then
 // pairwise merges of sorted runs in global memory through alt[0, n) for longer buckets.
-// Only wave-level barriers are used (the caller's workgroup is this one wave).
+// One wave calls it (of a workgroup of any size).
 // Sorts a bucket of n <= 64 distinct entries seg[0, n) ascending with one wave: each lane
 // takes one entry, counts the bucket's entries below it (its rank) from broadcast reads of
 // the whole bucket in LDS, and stores it at its rank, into `out` (LDS, kept for the caller)
@@ -305,7 +314,7 @@ __device__ __forceinline__ void rank_sort64(uint32_t* __restrict__ seg, int n,
   const int lane = threadIdx.x & 63;
   const uint32_t e = lane < n ? seg[lane] : 0xFFFFFFFFu;
   scratch[lane] = e;  // padding above n: no entry is greater
-  __syncthreads();
+  wave_sync();
   int rank = 0;
   const uint4* s4 = reinterpret_cast<const uint4*>(scratch);
   for (int j = 0; j < (n + 3) >> 2; ++j) {
@@ -317,7 +326,7 @@ __device__ __forceinline__ void rank_sort64(uint32_t* __restrict__ seg, int n,
     seg[rank] = e;
   }
   __threadfence_block();
-  __syncthreads();
+  wave_sync();
 }
 
 __device__ __forceinline__ void sort_bucket(uint32_t* __restrict__ seg, uint32_t* __restrict__ alt,
@@ -329,7 +338,7 @@ __device__ __forceinline__ void sort_bucket(uint32_t* __restrict__ seg, uint32_t
     int p2 = 1;
     while (p2 < m) p2 <<= 1;
     for (int i = lane; i < p2; i += 64) lds[i] = (i < m) ? seg[c0 + i] : 0xFFFFFFFFu;
-    __syncthreads();
+    wave_sync();
     for (int k = 2; k <= p2; k <<= 1) {
       for (int jj = k >> 1; jj > 0; jj >>= 1) {
         for (int i = lane; i < p2; i += 64) {
@@ -342,12 +351,12 @@ __device__ __forceinline__ void sort_bucket(uint32_t* __restrict__ seg, uint32_t
             }
           }
         }
-        __syncthreads();
+        wave_sync();
       }
     }
     for (int i = lane; i < m; i += 64) seg[c0 + i] = lds[i];
     __threadfence_block();
-    __syncthreads();
+    wave_sync();
   }
   if (n <= run) return;
   // An element's output position is its index in its own run plus the number of smaller
@@ -371,7 +380,7 @@ __device__ __forceinline__ void sort_bucket(uint32_t* __restrict__ seg, uint32_t
       dst[pair_lo + (i - r_i * width) + (lo - o_lo)] = v;
     }
     __threadfence_block();
-    __syncthreads();
+    wave_sync();
     uint32_t* tmp = src;
     src = dst;
     dst = tmp;
@@ -379,7 +388,7 @@ __device__ __forceinline__ void sort_bucket(uint32_t* __restrict__ seg, uint32_t
   if (src != seg) {
     for (int i = lane; i < n; i += 64) seg[i] = src[i];
     __threadfence_block();
-    __syncthreads();
+    wave_sync();
   }
 }
 

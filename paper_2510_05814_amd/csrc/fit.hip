@@ -4,7 +4,7 @@
 // A fit step runs three kernels (a fit's first step computes the render records first): the
 // scatter of the (block, kernel) pairs into fixed-width block buckets, over each kernel's
 // block rectangle computed from its model row (binning.hip), then
-//   k_fit_tile: one wave per 16x16 block orders the block's bucket, renders the block
+//   k_fit_tile: one wave (four on small rasters) per 16x16 block orders the block's bucket, renders the block
 //     (image, D, squared error) and runs the backward over the same list while the
 //     pixels' y, D and dL/dy are still in its registers -- the backward of a block needs
 //     only that block's pixels, so nothing round-trips through HBM between the two;
@@ -39,21 +39,39 @@ struct FitTileArgs {
   float* __restrict__ pair_grads;
 };
 
-template <int C, int ORDER, bool RBF, int TRUNC>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8, 8)))
+// WAVES waves per block (tile_math.h).  One-wave workgroups are held to 64 VGPRs, 8 waves per
+// SIMD.
+template <int C, int ORDER, bool RBF, int TRUNC, int WAVES>
+__global__ __launch_bounds__(kWave * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 1 ? 8 : 4, 8)))
 void k_fit_tile(FitTileArgs a) {
+  constexpr int ROWS = kStrips / WAVES;
   constexpr int LDS_FLOATS = kChunk * record_stride(C, ORDER);
   static_assert(LDS_FLOATS >= 64, "the rank sort's scratch lives in the record buffer");
   // the forward's records, then the backward's pixel seeds
   constexpr int LDS_BYTES = max_of(LDS_FLOATS * 4, kTilePixels * (int)sizeof(PixelSeed<C>));
   __shared__ float4 srec[LDS_BYTES / 16];
   __shared__ __align__(16) BackwardScratch sc;  // sc.ent: also the entries of the chunk being staged
+  __shared__ float s_err[WAVES == 1 ? 1 : kTilePixels];
   const int tile = xcd_block(blockIdx.x, a.S.T);
   const int t0 = a.status[kStepShadow];
+  const int wave = wave_index<WAVES>();
   // The bucket's fill count; the cursor is then reset for the next step's scatter (the store
-  // depends on the loaded value, so it cannot overtake the load).
-  const int cnt = a.cursors[tile];
-  if (threadIdx.x == 0 && cnt >= 0) a.cursors[tile] = 0;
+  // depends on the loaded value, so it cannot overtake the load; with several waves one
+  // thread loads it for all).
+  int cnt;
+  if (WAVES == 1) {
+    cnt = a.cursors[tile];
+    if (threadIdx.x == 0 && cnt >= 0) a.cursors[tile] = 0;
+  } else {
+    if (threadIdx.x == 0) {
+      const int c = a.cursors[tile];
+      sc.ent[0] = (uint32_t)c;
+      if (c >= 0) a.cursors[tile] = 0;
+    }
+    __syncthreads();
+    cnt = __builtin_amdgcn_readfirstlane((int)sc.ent[0]);
+    __syncthreads();
+  }
   if (a.status[kStepFlags + (t0 & 1)] != 0) {
     // Some bucket overflowed: nothing is rendered or updated this step.  The status words
     // report the storage a step needs (blocks x longest bucket).
@@ -74,34 +92,38 @@ void k_fit_tile(FitTileArgs a) {
   // Order the bucket (the scatter appended in arbitrary order).  A bucket of one chunk is
   // ranked in registers and kept in LDS for the forward's staging.
   constexpr int run = LDS_FLOATS >= 1024 ? 1024 : (LDS_FLOATS >= 512 ? 512 : 256);
-  if (rg.y - rg.x <= kChunk) {
+  if (wave != 0) {
+    // (the first wave sorts)
+  } else if (rg.y - rg.x <= kChunk) {
     rank_sort64(a.vals + rg.x, rg.y - rg.x, reinterpret_cast<uint32_t*>(srec), sc.ent);
   } else {
     sort_bucket(a.vals + rg.x, a.vals_alt + rg.x, rg.y - rg.x, reinterpret_cast<uint32_t*>(srec),
                 run);
   }
+  __syncthreads();
 
-  const PixelCoords px = lane_pixels(sg, tile - sg.tile_offset);
-  float D[kRows], N[kRows][C];
+  const PixelCoords<ROWS> px = lane_pixels<WAVES>(sg, tile - sg.tile_offset);
+  float D[ROWS], N[ROWS][C];
   const BlockBox bb = block_box(sg, tile - sg.tile_offset);
-  forward_accumulate<C, ORDER, TRUNC>(px, bb, a.S.r2, a.S.cut_scale, a.S.cut_offset, a.records,
+  forward_accumulate<C, ORDER, TRUNC, WAVES>(px, bb, a.S.r2, a.S.cut_scale, a.S.cut_offset, a.records,
                                       a.vals, a.shift, rg, srec, D, N, sc.ent);
 
   const int lane = threadIdx.x & 63;
   PixelSeed<C>* seeds = reinterpret_cast<PixelSeed<C>*>(srec);
   __syncthreads();  // the records are read: their place takes the seeds
-  const BlockPixels bp = block_pixels(sg, tile - sg.tile_offset);
+  const BlockPixels bp = block_pixels<WAVES>(sg, tile - sg.tile_offset);
   const PixelValue<C>* tgt = reinterpret_cast<const PixelValue<C>*>(a.target) + bp.base;
-  bool in[kRows];
-  PixelValue<C> t[kRows], y[kRows];
+  bool in[ROWS];
+  PixelValue<C> t[ROWS], y[ROWS];
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
     in[i] = in_raster(px.u, px.v0 + 4 * i, sg);
     if (in[i]) t[i] = tgt[bp.off + i * bp.step];
   }
-  float err = 0.0f;
+  float err[ROWS];
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
+    err[i] = 0.0f;
     PixelSeed<C> sd;
     sd.gy = 0.0f;
 #pragma unroll
@@ -116,7 +138,7 @@ void k_fit_tile(FitTileArgs a) {
         const float yc = RBF ? N[i][c] : (cov ? div_refined(N[i][c], D[i], invD) : 0.0f);
         y[i].v[c] = yc;
         const float d = yc - t[i].v[c];
-        err = __builtin_fmaf(d, d, err);
+        err[i] = __builtin_fmaf(d, d, err[i]);
         if (cov) {
           const float g = d * inv_n2;
           if (!RBF) sd.gy = __builtin_fmaf(g, yc, sd.gy);
@@ -125,25 +147,25 @@ void k_fit_tile(FitTileArgs a) {
       }
       sd.gy = sd.gy * invD;
     }
-    seeds[((lane >> 4) + 4 * i) * kTile + (lane & 15)] = sd;
+    seeds[((lane >> 4) + 4 * (i + ROWS * wave)) * kTile + (lane & 15)] = sd;
   }
   if (a.image) {
     PixelValue<C>* img = reinterpret_cast<PixelValue<C>*>(a.image) + bp.base;
     float* den = a.denom + bp.base;
 #pragma unroll
-    for (int i = 0; i < kRows; ++i) {
+    for (int i = 0; i < ROWS; ++i) {
       if (in[i]) {
         img[bp.off + i * bp.step] = y[i];
         den[bp.off + i * bp.step] = D[i];
       }
     }
   }
-  for (int off = 32; off > 0; off >>= 1) err += __shfl_xor(err, off);
-  if (threadIdx.x == 0) a.tile_loss[tile] = err * inv_n;
+  const float sum = block_error<WAVES>(err, s_err);
+  if (threadIdx.x == 0) a.tile_loss[tile] = sum * inv_n;
 
   // each partial row goes to the row its entry names, where Adam reads it
   const float2 o = block_base(sg, tile - sg.tile_offset);
-  backward_accumulate<C, ORDER, true>(bb, o.x, o.y, 1.0f, a.S.r,
+  backward_accumulate<C, ORDER, true, WAVES>(bb, o.x, o.y, 1.0f, a.S.r,
                                       a.S.r2, a.records, a.vals, a.shift, true, rg, seeds, sc, true,
                                       a.pair_grads, a.S.K);
 }
@@ -328,7 +350,10 @@ hipError_t launch_fit_tile(const smoe_fit_state& st, const Segs& S, int width, i
                 b.tile_loss, b.pair_grads};
   with_shape(st.C, st.order, S, [&](auto sh) {
     using T = decltype(sh);
-    k_fit_tile<T::C, T::ORDER, T::RBF, T::TRUNC><<<S.T, kWave, 0, s>>>(a);
+    if (S.T <= kSplitForward)
+      k_fit_tile<T::C, T::ORDER, T::RBF, T::TRUNC, 4><<<S.T, 4 * kWave, 0, s>>>(a);
+    else
+      k_fit_tile<T::C, T::ORDER, T::RBF, T::TRUNC, 1><<<S.T, kWave, 0, s>>>(a);
   });
   return hipGetLastError();
 }

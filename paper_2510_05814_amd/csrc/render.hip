@@ -1,6 +1,6 @@
 // Forward rasterization of the SMoE regression (Eq. 3-5) on gfx950: the standalone render.
 //
-// One wave (64 lanes) per 16x16 block (lane layout in tile_math.h).  The block's kernel
+// One wave (64 lanes; four on small rasters) per 16x16 block (lane layout in tile_math.h).  The block's kernel
 // list is staged through LDS in chunks of 64 render records (coalesced float4 loads); the
 // wave reads each record with a uniform LDS address (a broadcast) and accumulates, in FP32
 // registers, the gate denominator D = sum_j pi_j K_j(x) and the numerators
@@ -38,18 +38,21 @@ constexpr int kSplitMin = 2 * kChunk;
 constexpr int kSplitWaves = 4;
 
 // Writes the block's pixels (y from N and D, Eq. 2-4 or Eq. 1) and its squared error.
-template <int C, bool RBF>
+// part: as for block_error.
+template <int C, bool RBF, int WAVES>
 __device__ __forceinline__ void render_epilogue(const RenderArgs& a, const SegGrid& sg,
-                                                const PixelCoords& px, int tile,
-                                                const float (&D)[kRows],
-                                                const float (&N)[kRows][C]) {
-  const BlockPixels bp = block_pixels(sg, tile - sg.tile_offset);
+                                                const PixelCoords<kStrips / WAVES>& px, int tile,
+                                                const float (&D)[kStrips / WAVES],
+                                                const float (&N)[kStrips / WAVES][C], float* part) {
+  constexpr int ROWS = kStrips / WAVES;
+  const BlockPixels bp = block_pixels<WAVES>(sg, tile - sg.tile_offset);
   PixelValue<C>* img = reinterpret_cast<PixelValue<C>*>(a.image) + bp.base;
   const PixelValue<C>* tgt = reinterpret_cast<const PixelValue<C>*>(a.target) + bp.base;
   float* den = a.denom + bp.base;
-  float err = 0.0f;
+  float err[ROWS];
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
+    err[i] = 0.0f;
     if (in_raster(px.u, px.v0 + 4 * i, sg)) {
       const int p = bp.off + i * bp.step;
       PixelValue<C> y;
@@ -64,7 +67,7 @@ __device__ __forceinline__ void render_epilogue(const RenderArgs& a, const SegGr
 #pragma unroll
         for (int c = 0; c < C; ++c) {
           const float d = y.v[c] - t.v[c];
-          err = __builtin_fmaf(d, d, err);
+          err[i] = __builtin_fmaf(d, d, err[i]);
         }
       }
       img[p] = y;
@@ -72,24 +75,26 @@ __device__ __forceinline__ void render_epilogue(const RenderArgs& a, const SegGr
     }
   }
   if (a.tile_loss) {
-    for (int off = 32; off > 0; off >>= 1) err += __shfl_xor(err, off);
-    if ((threadIdx.x & 63) == 0) a.tile_loss[tile] = err;
+    const float sum = block_error<WAVES>(err, part);
+    if (threadIdx.x == 0) a.tile_loss[tile] = sum;
   }
 }
 
-template <int C, int ORDER, bool RBF, int TRUNC>
-__global__ __launch_bounds__(kWave) void k_render(RenderArgs a) {
+template <int C, int ORDER, bool RBF, int TRUNC, int WAVES>
+__global__ __launch_bounds__(kWave * WAVES) void k_render(RenderArgs a) {
+  constexpr int ROWS = kStrips / WAVES;
+  __shared__ float s_err[WAVES == 1 ? 1 : kTilePixels];
   __shared__ float4 srec[kChunk * record_stride(C, ORDER) / 4];
   const int tile = xcd_block(blockIdx.x, a.S.T);
   const int2 rg = a.ranges[tile];
   if (rg.y - rg.x > kSplitMin) return;  // a long list: k_render_wide renders this block
   const SegGrid sg = seg_of_tile(a.S, tile);
-  const PixelCoords px = lane_pixels(sg, tile - sg.tile_offset);
-  float D[kRows], N[kRows][C];
-  forward_accumulate<C, ORDER, TRUNC>(px, block_box(sg, tile - sg.tile_offset), a.S.r2,
-                                      a.S.cut_scale, a.S.cut_offset, a.records, a.vals, 0, rg, srec,
-                                      D, N);
-  render_epilogue<C, RBF>(a, sg, px, tile, D, N);
+  const PixelCoords<ROWS> px = lane_pixels<WAVES>(sg, tile - sg.tile_offset);
+  float D[ROWS], N[ROWS][C];
+  forward_accumulate<C, ORDER, TRUNC, WAVES>(px, block_box(sg, tile - sg.tile_offset), a.S.r2,
+                                             a.S.cut_scale, a.S.cut_offset, a.records, a.vals, 0,
+                                             rg, srec, D, N);
+  render_epilogue<C, RBF, WAVES>(a, sg, px, tile, D, N, s_err);
 }
 
 // Four waves per block for lists longer than kSplitMin.  Each wave stages its own records
@@ -104,16 +109,16 @@ constexpr int kWideGroups = 1024;
 template <int C, int ORDER, bool RBF, int TRUNC>
 __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile, int2 rg,
                                                   float4 (*srec)[kChunk * record_stride(C, ORDER) / 4],
-                                                  float (*part)[kRows * (1 + C)][kWave]) {
+                                                  float (*part)[kStrips * (1 + C)][kWave]) {
   constexpr int RS = record_stride(C, ORDER);
   constexpr int Q = RS / 4;
   const int len = rg.y - rg.x;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const SegGrid sg = seg_of_tile(a.S, tile);
-  const PixelCoords px = lane_pixels(sg, tile - sg.tile_offset);
+  const PixelCoords<kStrips> px = lane_pixels<1>(sg, tile - sg.tile_offset);
   const int per = (len + kSplitWaves - 1) / kSplitWaves;
   const int b = rg.x + min(len, wv * per), e = rg.x + min(len, (wv + 1) * per);
-  float D[kRows], N[kRows][C];
+  float D[kStrips], N[kStrips][C];
   zero_sums<C>(D, N);
   const float cut_scale = in_vgpr(a.S.cut_scale), cut_offset = in_vgpr(a.S.cut_offset);
   float4* my = srec[wv];
@@ -128,11 +133,11 @@ __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile,
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    forward_chunk<C, ORDER, TRUNC>(px, bb, a.S.r2, cut_scale, cut_offset, my, n, D, N);
+    forward_chunk<C, ORDER, TRUNC, kStrips>(px, bb, a.S.r2, cut_scale, cut_offset, my, n, D, N);
   }
   if (wv > 0) {
 #pragma unroll
-    for (int i = 0; i < kRows; ++i) {
+    for (int i = 0; i < kStrips; ++i) {
       part[wv - 1][i * (1 + C)][lane] = D[i];
 #pragma unroll
       for (int c = 0; c < C; ++c) part[wv - 1][i * (1 + C) + 1 + c][lane] = N[i][c];
@@ -143,13 +148,13 @@ __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile,
 #pragma unroll
     for (int w = 0; w < kSplitWaves - 1; ++w) {
 #pragma unroll
-      for (int i = 0; i < kRows; ++i) {
+      for (int i = 0; i < kStrips; ++i) {
         D[i] += part[w][i * (1 + C)][lane];
 #pragma unroll
         for (int c = 0; c < C; ++c) N[i][c] += part[w][i * (1 + C) + 1 + c][lane];
       }
     }
-    render_epilogue<C, RBF>(a, sg, px, tile, D, N);
+    render_epilogue<C, RBF, 1>(a, sg, px, tile, D, N, nullptr);
   }
   __syncthreads();  // part is reused by the next block of the walk
 }
@@ -157,7 +162,7 @@ __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile,
 template <int C, int ORDER, bool RBF, int TRUNC>
 __global__ __launch_bounds__(kSplitWaves * kWave) void k_render_wide(RenderArgs a) {
   __shared__ float4 srec[kSplitWaves][kChunk * record_stride(C, ORDER) / 4];
-  __shared__ float part[kSplitWaves - 1][kRows * (1 + C)][kWave];
+  __shared__ float part[kSplitWaves - 1][kStrips * (1 + C)][kWave];
   // the binning recorded the longest list: without a long one there is nothing to walk
   if (a.status[2] <= kSplitMin) return;
   for (int tile = blockIdx.x; tile < a.S.T; tile += gridDim.x) {
@@ -252,7 +257,10 @@ hipError_t launch_render(int C, int order, const Segs& S, const smoe_bins& b, fl
                b.status};
   with_shape(C, order, S, [&](auto sh) {
     using T = decltype(sh);
-    k_render<T::C, T::ORDER, T::RBF, T::TRUNC><<<S.T, kWave, 0, s>>>(a);
+    if (S.T <= kSplitForward)
+      k_render<T::C, T::ORDER, T::RBF, T::TRUNC, 4><<<S.T, 4 * kWave, 0, s>>>(a);
+    else
+      k_render<T::C, T::ORDER, T::RBF, T::TRUNC, 1><<<S.T, kWave, 0, s>>>(a);
     k_render_wide<T::C, T::ORDER, T::RBF, T::TRUNC>
         <<<min(S.T, kWideGroups), kSplitWaves * kWave, 0, s>>>(a);
   });

@@ -1,10 +1,12 @@
 // Per-block math of the rasterized SMoE on gfx950, shared by the standalone render and
 // backward calls and the fused fit-step kernel.  Internal header.
 //
-// Lane layout: one wave per 16x16 block; lane l owns column l & 15 and the four rows
-// (l >> 4) + 4i, i = 0..3.  The column-only terms of the exact truncation test (dx, z1,
-// l21 z1, z1^2) are then computed once per kernel for the lane's four pixels, and a wave
-// iteration i covers one 16x4 strip of the block.
+// Lane layout of the forward: a block is four 16x4 strips, strip i the rows (l >> 4) + 4i of
+// lane l, which owns column l & 15.  One wave takes all four strips -- the column's terms
+// (dx, z1, l21 z1, z1^2) are then computed once per kernel for four pixels -- or, on rasters of
+// too few blocks to fill the chip that way, four waves take a strip each (WAVES).  Either way a
+// pixel's sums are formed by one lane over the whole list in the same operations, so the
+// results are the same bits.
 #pragma once
 
 #include <type_traits>
@@ -42,13 +44,30 @@ inline void with_shape(int C, int order, const Segs& S, F&& f) {
   else with_mode<3, 1>(S, f);
 }
 constexpr int kChunk = 64;                     // records staged in LDS per chunk
-constexpr int kRows = kTilePixels / kWave;     // pixels per lane (4)
+constexpr int kStrips = kTilePixels / kWave;   // 16x4 strips of a block (4)
 
+// Waves per block: one, or four (a strip each) on rasters whose blocks alone leave SIMDs idle
+// (1024 of them).  Four waves pay the column's terms four times over, one per SIMD waits on
+// its own latencies.  Measured, one wave against four, at 1024 / 1600 / 2025 / 2500 blocks:
+// RGB linear fit step 30.1 / 31.9 / 32.9 / 36.5 us against 26.8 / 30.8 / 33.3 / 37.7, render
+// 14.3 / 14.2 / 14.1 / 14.6 against 14.2 / 14.3 / 15.7 / 18.3.  The backward alone has no such
+// terms (its groups of entries are dealt out whole): 16.0 us against 13.8 at 1024 blocks, 24.1
+// against 24.0 at 3600, 30.1 against 28.7 at 5184, 37.1 against 37.9 at 7744.
+constexpr int kSplitForward = 1536, kSplitBackward = 6144;
+
+// The wave's index in its workgroup, wave-uniform.
+template <int WAVES>
+__device__ __forceinline__ int wave_index() {
+  return WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
+// ROWS: the lane's pixels, one per strip its wave takes.
+template <int ROWS>
 struct PixelCoords {
   int u;            // output column of the lane (within its raster; < 0 or >= W: outside)
   int v0;           // output row of the lane's first pixel (rows v0 + 4i)
   float x;          // sampling coordinates
-  float y[kRows];
+  float y[ROWS];
 };
 
 // A pixel's C channel values, moved as one load or store of 4 C bytes.  RGB: one 12-byte
@@ -81,23 +100,26 @@ __device__ __forceinline__ bool in_raster(int u, int v, const SegGrid& g) {
 // multiple (binary32 sample coordinates included, over the whole accepted range of origins,
 // sizes and scales), so all of a block's points lie in one native block and every kernel of
 // its list is a member at every one of them: no per-point membership test.
-__device__ __forceinline__ PixelCoords lane_pixels(const SegGrid& g, int tile) {
-  PixelCoords p;
+template <int WAVES>
+__device__ __forceinline__ PixelCoords<kStrips / WAVES> lane_pixels(const SegGrid& g, int tile) {
+  constexpr int ROWS = kStrips / WAVES;
+  PixelCoords<ROWS> p;
   const int lane = threadIdx.x & 63;
   const int tx = tile % g.ntx, ty = tile / g.ntx;
   p.u = kTile * (g.bx0 + tx) - g.ox + (lane & 15);
-  p.v0 = kTile * (g.by0 + ty) - g.oy + (lane >> 4);
+  p.v0 = kTile * (g.by0 + ty) - g.oy + (lane >> 4) + 4 * ROWS * wave_index<WAVES>();
   p.x = sample_coord(p.u, g.ox, g.inv_s);
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) p.y[i] = sample_coord(p.v0 + 4 * i, g.oy, g.inv_s);
+  for (int i = 0; i < ROWS; ++i) p.y[i] = sample_coord(p.v0 + 4 * i, g.oy, g.inv_s);
   return p;
 }
 
+template <int WAVES>
 __device__ __forceinline__ BlockPixels block_pixels(const SegGrid& g, int tile) {
   const int lane = threadIdx.x & 63;
   const int u = kTile * (g.bx0 + tile % g.ntx) - g.ox, v = kTile * (g.by0 + tile / g.ntx) - g.oy;
-  return BlockPixels{g.pixel_offset + (long long)v * g.W + u, (lane >> 4) * g.W + (lane & 15),
-                     4 * g.W};
+  const int row = (lane >> 4) + 4 * (kStrips / WAVES) * wave_index<WAVES>();
+  return BlockPixels{g.pixel_offset + (long long)v * g.W + u, row * g.W + (lane & 15), 4 * g.W};
 }
 
 // A wave-uniform value moved to a scalar register (it then holds no vector register over the
@@ -126,25 +148,25 @@ __device__ __forceinline__ float2 block_base(const SegGrid& g, int tile) {
                      (float)(kTile * (g.by0 + tile / g.ntx)) + 0.5f);
 }
 
-// The lane's index, opaque to the compiler: what the once-per-chunk code derives from it is then
-// computed there instead of being held in registers across the loops over entries.
-__device__ __forceinline__ int local_lane() {
-  int lane = threadIdx.x & 63;
-  asm volatile("" : "+v"(lane));
-  return lane;
+// The thread's index, opaque to the compiler: what the once-per-chunk code derives from it is
+// then computed there instead of being held in registers across the loops over entries.
+__device__ __forceinline__ int local_thread() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
 }
 
-// Stages the records of list entries [base, base + n) (n <= kChunk) into LDS.  An entry
-// holds the kernel id shifted left by `shift` (the fit step's packed bucket entries; 0
-// elsewhere).
-template <int RS>
+// Stages the records of list entries [base, base + n) (n <= kChunk) into LDS, with all threads
+// of the workgroup.  An entry holds the kernel id shifted left by `shift` (the fit step's
+// packed bucket entries; 0 elsewhere).
+template <int RS, int WAVES>
 __device__ __forceinline__ void stage_records(float4* __restrict__ srec,
                                               const float* __restrict__ records,
                                               const uint32_t* __restrict__ vals, int base, int n,
                                               int shift) {
   constexpr int Q = RS / 4;
   __syncthreads();
-  for (int i = local_lane(); i < n * Q; i += kWave) {
+  for (int i = local_thread(); i < n * Q; i += kWave * WAVES) {
     const int k = i / Q, c = i - k * Q;
     srec[i] = reinterpret_cast<const float4*>(records + (size_t)(vals[base + k] >> shift) * RS)[c];
   }
@@ -153,7 +175,7 @@ __device__ __forceinline__ void stage_records(float4* __restrict__ srec,
 
 // The same with the entries in LDS: ent[k] is entry base + k, copied there from vals first
 // unless `ready` (the caller's sort left the list there).
-template <int RS>
+template <int RS, int WAVES>
 __device__ __forceinline__ void stage_records_lds(float4* __restrict__ srec,
                                                   const float* __restrict__ records,
                                                   const uint32_t* __restrict__ vals, int base,
@@ -162,11 +184,11 @@ __device__ __forceinline__ void stage_records_lds(float4* __restrict__ srec,
   constexpr int Q = RS / 4;
   __syncthreads();
   if (!ready) {
-    const int lane = local_lane();
-    if (lane < n) ent[lane] = vals[base + lane];
+    const int t = local_thread();
+    if (t < n) ent[t] = vals[base + t];
     __syncthreads();
   }
-  for (int i = local_lane(); i < n * Q; i += kWave) {
+  for (int i = local_thread(); i < n * Q; i += kWave * WAVES) {
     const int k = i / Q, c = i - k * Q;
     srec[i] = reinterpret_cast<const float4*>(records + (size_t)(ent[k] >> shift) * RS)[c];
   }
@@ -180,7 +202,7 @@ __device__ __forceinline__ void stage_records_lds(float4* __restrict__ srec,
 // their kernels have no such entry.
 template <int RS>
 __device__ __forceinline__ uint64_t far_entries(const BlockBox& bb, const float4* srec, int n) {
-  const int lane = local_lane();
+  const int lane = local_thread() & 63;
   bool far = false;
   if (lane < n) {
     const float4 f = srec[lane * (RS / 4)], g = srec[lane * (RS / 4) + 1];
@@ -213,10 +235,10 @@ __device__ __forceinline__ uint64_t far_entries(const BlockBox& bb, const float4
 // below -2^43 otherwise: exp2 of an excluded term is exactly zero.
 // Measured: binning and render of a 2048^2 model with 65536 kernels 88.5 -> 83.7 us, its fit
 // step 116.1 -> 114.6 us, a 512^2 render with lists of several hundred 332 -> 320 us.
-template <int C, int ORDER, int TRUNC>
-__device__ __forceinline__ void forward_entry(const PixelCoords& px, float r2, float cut_scale,
+template <int C, int ORDER, int TRUNC, int ROWS>
+__device__ __forceinline__ void forward_entry(const PixelCoords<ROWS>& px, float r2, float cut_scale,
                                               float cut_offset, const float4* f4, bool far,
-                                              float (&D)[kRows], float (&N)[kRows][C]) {
+                                              float (&D)[ROWS], float (&N)[ROWS][C]) {
   constexpr int RS = record_stride(C, ORDER);
   float r[RS];
 #pragma unroll
@@ -237,46 +259,48 @@ __device__ __forceinline__ void forward_entry(const PixelCoords& px, float r2, f
   for (int c = 0; c < C; ++c)
     mx[c] = ORDER == 1 ? __builtin_fmaf(r[kRecExpert + C + c], dx, r[kRecExpert + c])
                        : r[kRecExpert + c];
-  float dy[kRows], a[kRows];
+  float dy[ROWS], a[ROWS];
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) dy[i] = px.y[i] - r[1];
+  for (int i = 0; i < ROWS; ++i) dy[i] = px.y[i] - r[1];
   // pi K = exp(rho - q/2) = exp2(rho log2 e - q log2 e / 2)
   if (TRUNC == SMOE_TRUNC_GRADIENT && !far) {
     constexpr float kRoot = 0.84932180028801904272f;  // sqrt(log2(e) / 2)
     const float kk = r[4] * kRoot;
     const float alpha = __builtin_fmaf(zz1, -0.5f * kLog2e, r[5]);
 #pragma unroll
-    for (int i = 0; i < kRows; ++i) {
+    for (int i = 0; i < ROWS; ++i) {
       const float v = (dy[i] - tt) * kk;
       a[i] = __builtin_fmaf(-v, v, alpha);
     }
   } else {
-    float q[kRows];
+    float q[ROWS];
 #pragma unroll
-    for (int i = 0; i < kRows; ++i) {
+    for (int i = 0; i < ROWS; ++i) {
       const float w = dy[i] - tt;
       const float z2 = w * r[4];
       q[i] = zz1 + z2 * z2;
     }
     if (TRUNC == SMOE_TRUNC_RENDER) {
-      const float qmax = __builtin_fmaxf(__builtin_fmaxf(q[0], q[1]), __builtin_fmaxf(q[2], q[3]));
+      float qmax = q[0];
+#pragma unroll
+      for (int i = 1; i < ROWS; ++i) qmax = __builtin_fmaxf(qmax, q[i]);
       if (__any(!(qmax <= r2))) {
 #pragma unroll
-        for (int i = 0; i < kRows; ++i)
+        for (int i = 0; i < ROWS; ++i)
           q[i] = __builtin_fmaxf(q[i], __builtin_fmaf(q[i], cut_scale, cut_offset));
       }
 #pragma unroll
-      for (int i = 0; i < kRows; ++i) a[i] = __builtin_fmaf(q[i], -0.5f * kLog2e, r[5]);
+      for (int i = 0; i < ROWS; ++i) a[i] = __builtin_fmaf(q[i], -0.5f * kLog2e, r[5]);
     } else {
 #pragma unroll
-      for (int i = 0; i < kRows; ++i) {
+      for (int i = 0; i < ROWS; ++i) {
         a[i] = __builtin_fmaf(q[i], -0.5f * kLog2e, r[5]);
         a[i] = __builtin_fminf(a[i], __builtin_fmaf(a[i], cut_scale, cut_offset));
       }
     }
   }
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
     const float e = __builtin_amdgcn_exp2f(a[i]);
     D[i] += e;
 #pragma unroll
@@ -289,16 +313,16 @@ __device__ __forceinline__ void forward_entry(const PixelCoords& px, float r2, f
 }
 
 // The entries of a staged chunk, in order.
-template <int C, int ORDER, int TRUNC>
-__device__ __forceinline__ void forward_chunk(const PixelCoords& px, const BlockBox& bb, float r2,
+template <int C, int ORDER, int TRUNC, int ROWS>
+__device__ __forceinline__ void forward_chunk(const PixelCoords<ROWS>& px, const BlockBox& bb, float r2,
                                               float cut_scale, float cut_offset,
-                                              const float4* srec, int n, float (&D)[kRows],
-                                              float (&N)[kRows][C]) {
+                                              const float4* srec, int n, float (&D)[ROWS],
+                                              float (&N)[ROWS][C]) {
   constexpr int RS = record_stride(C, ORDER);
   constexpr int Q = RS / 4;
   const uint64_t far = TRUNC == SMOE_TRUNC_GRADIENT ? far_entries<RS>(bb, srec, n) : 0;
   for (int k = 0; k < n; ++k)
-    forward_entry<C, ORDER, TRUNC>(px, r2, cut_scale, cut_offset, &srec[k * Q],
+    forward_entry<C, ORDER, TRUNC, ROWS>(px, r2, cut_scale, cut_offset, &srec[k * Q],
                                    (far >> k & 1) != 0, D, N);
 }
 
@@ -309,10 +333,10 @@ __device__ __forceinline__ float in_vgpr(float x) {
   return x;
 }
 
-template <int C>
-__device__ __forceinline__ void zero_sums(float (&D)[kRows], float (&N)[kRows][C]) {
+template <int C, int ROWS>
+__device__ __forceinline__ void zero_sums(float (&D)[ROWS], float (&N)[ROWS][C]) {
 #pragma unroll
-  for (int i = 0; i < kRows; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
     D[i] = 0.0f;
 #pragma unroll
     for (int c = 0; c < C; ++c) N[i][c] = 0.0f;
@@ -324,13 +348,13 @@ __device__ __forceinline__ void zero_sums(float (&D)[kRows], float (&N)[kRows][C
 // shift: list entries hold the kernel id << shift.  ent: null, or LDS room for one chunk of
 // entries, which the staging then reads from there (a single-chunk list already holds them,
 // sorted; longer lists copy each chunk's entries in).
-template <int C, int ORDER, int TRUNC>
-__device__ __forceinline__ void forward_accumulate(const PixelCoords& px, const BlockBox& bb,
+template <int C, int ORDER, int TRUNC, int WAVES>
+__device__ __forceinline__ void forward_accumulate(const PixelCoords<kStrips / WAVES>& px, const BlockBox& bb,
                                                    float r2, float cut_scale, float cut_offset,
                                                    const float* __restrict__ records,
                                                    const uint32_t* __restrict__ vals, int shift,
-                                                   int2 rg, float4* srec, float (&D)[kRows],
-                                                   float (&N)[kRows][C],
+                                                   int2 rg, float4* srec, float (&D)[kStrips / WAVES],
+                                                   float (&N)[kStrips / WAVES][C],
                                                    uint32_t* ent = nullptr) {
   constexpr int RS = record_stride(C, ORDER);
   zero_sums<C>(D, N);
@@ -340,9 +364,9 @@ __device__ __forceinline__ void forward_accumulate(const PixelCoords& px, const 
   }
   for (int base = rg.x; base < rg.y; base += kChunk) {
     const int n = __builtin_amdgcn_readfirstlane(min(kChunk, rg.y - base));
-    if (ent) stage_records_lds<RS>(srec, records, vals, base, n, shift, ent, rg.y - rg.x <= kChunk);
-    else stage_records<RS>(srec, records, vals, base, n, shift);
-    forward_chunk<C, ORDER, TRUNC>(px, bb, r2, cut_scale, cut_offset, srec, n, D, N);
+    if (ent) stage_records_lds<RS, WAVES>(srec, records, vals, base, n, shift, ent, rg.y - rg.x <= kChunk);
+    else stage_records<RS, WAVES>(srec, records, vals, base, n, shift);
+    forward_chunk<C, ORDER, TRUNC, kStrips / WAVES>(px, bb, r2, cut_scale, cut_offset, srec, n, D, N);
   }
 }
 
@@ -541,6 +565,30 @@ __device__ __forceinline__ float row_reduce16_masked(float (&v)[16]) {
   return keep + dpp<0xB1>(send);
 }
 
+// A block's squared error from the strips' (err: the lane's, of the strips its wave takes): per
+// lane ((strip 0 + 1) + (2 + 3)), then a butterfly over the lanes -- one order however many
+// waves take the block.  Returns it in every lane of wave 0.  part: kTilePixels floats of LDS
+// (unused by one wave); every thread calls it.
+template <int WAVES>
+__device__ __forceinline__ float block_error(const float (&err)[kStrips / WAVES], float* part) {
+  float e[kStrips];
+  if (WAVES == 1) {
+#pragma unroll
+    for (int i = 0; i < kStrips; ++i) e[i] = err[i % (kStrips / WAVES)];
+  } else {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < kStrips / WAVES; ++i)
+      part[(wave_index<WAVES>() * (kStrips / WAVES) + i) * kWave + lane] = err[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kStrips; ++i) e[i] = part[i * kWave + lane];
+  }
+  float t = (e[0] + e[1]) + (e[2] + e[3]);
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
+  return t;
+}
+
 // Adjoint seeds of a block's pixels in LDS, row-major: dL/dy_c / D and sum_c dL/dy_c y_c / D,
 // zero where no gradient flows (D = 0 or outside the raster).  With the seed 1/D -> 1 and
 // sum_c g_c y_c -> 0 the same backward is the adjoint of the un-normalised sum of Eq. (1):
@@ -629,7 +677,8 @@ struct BackwardScratch {
 // those as for the pairs.)  The 16 lanes cover the box of the entry's ellipse in the
 // block (ellipse_box, a lane per entry, 64 entries at once): a box of at most 8, 4 or 2
 // columns takes 2, 4 or 8 rows per step.  Entries are taken in the order of their step
-// counts (in pairs of steps), most first, so the four of a group need about as many.
+// counts (in pairs of steps), most first, so the four of a group need about as many; with
+// several waves to a block, they take the groups in turn.
 // Measured against one entry per wave: the 2048^2 RGB linear fit step 145 -> 117 us (65536
 // kernels, 26-entry lists), the standalone backward of a 509x381 render 20.3 -> 13.7 us.
 // The seeds sit in LDS, where the forward's records were; a lane reads its entry's record
@@ -646,7 +695,7 @@ struct BackwardScratch {
 // where the fit step's gather reads it; otherwise the entry's list position.
 // x0, y0: o + 0.5 + (column, row) of the block's first pixel, whose coordinates are these
 // times inv_s; UNIT: inv_s = 1.  ent_ready: sc.ent holds a single-chunk list already.
-template <int C, int ORDER, bool UNIT>
+template <int C, int ORDER, bool UNIT, int WAVES>
 __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0, float y0,
                                                     float inv_s, float radius, float r2,
                                                     const float* __restrict__ records,
@@ -661,52 +710,54 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
   constexpr int PS = partial_stride(NP);
   static_assert(PS <= 16, "16 accumulators per kernel");
   const int lane = threadIdx.x & 63;
-  const int l16 = lane & 15, sub = lane >> 4;
+  const int l16 = lane & 15, sub = lane >> 4, wave = wave_index<WAVES>();
   const uint32_t slot_mask = (1u << shift) - 1u;
   for (int base = rg.x; base < rg.y; base += kChunk) {
     const int n = __builtin_amdgcn_readfirstlane(min(kChunk, rg.y - base));
     __syncthreads();
-    // a lane per entry: its partial row, its box, its pairs of steps
-    uint32_t e = 0, row = 0;
-    int its = 0, packed_box = 0;
-    if (lane < n) {
-      e = ent_ready && rg.y - rg.x <= kChunk ? sc.ent[lane] : vals[base + lane];
-      const uint32_t low = e & slot_mask;
-      row = !packed ? (uint32_t)(base + lane)
-                    : (low < (uint32_t)kSlots ? (e >> shift) * (uint32_t)kSlots + low
-                                              : (uint32_t)K * kSlots + (uint32_t)rg.x + (low - kSlots));
-      const float4* r4 = reinterpret_cast<const float4*>(records + (size_t)(e >> shift) * RS);
-      const float4 f = r4[0];
-      const EllipseBox b = ellipse_box(bb, radius, f.x, f.y, f.z, f.w, r4[1].x);
-      if (b.row0 <= b.row1) {
-        const int lw = max(1, 32 - __clz(b.col1 - b.col0));  // columns <= 2^lw
-        const int lr = 4 - lw;                               // 2^lr rows per step
-        its = (b.row1 - b.row0 + (2 << lr)) >> (lr + 1);
-        // (the last steps' rows and columns stay inside the block)
-        packed_box = min(b.row0, 16 - (its << (lr + 1))) | min(b.col0, 16 - (1 << lw)) << 4 |
-                     lr << 8 | its << 12;
+    if (wave == 0) {
+      // a lane per entry: its partial row, its box, its pairs of steps
+      uint32_t e = 0, row = 0;
+      int its = 0, packed_box = 0;
+      if (lane < n) {
+        e = ent_ready && rg.y - rg.x <= kChunk ? sc.ent[lane] : vals[base + lane];
+        const uint32_t low = e & slot_mask;
+        row = !packed ? (uint32_t)(base + lane)
+                      : (low < (uint32_t)kSlots ? (e >> shift) * (uint32_t)kSlots + low
+                                                : (uint32_t)K * kSlots + (uint32_t)rg.x + (low - kSlots));
+        const float4* r4 = reinterpret_cast<const float4*>(records + (size_t)(e >> shift) * RS);
+        const float4 f = r4[0];
+        const EllipseBox b = ellipse_box(bb, radius, f.x, f.y, f.z, f.w, r4[1].x);
+        if (b.row0 <= b.row1) {
+          const int lw = max(1, 32 - __clz(b.col1 - b.col0));  // columns <= 2^lw
+          const int lr = 4 - lw;                               // 2^lr rows per step
+          its = (b.row1 - b.row0 + (2 << lr)) >> (lr + 1);
+          // (the last steps' rows and columns stay inside the block)
+          packed_box = min(b.row0, 16 - (its << (lr + 1))) | min(b.col0, 16 - (1 << lw)) << 4 |
+                       lr << 8 | its << 12;
+        }
       }
-    }
-    const uint32_t id = lane < n ? e >> shift : __builtin_amdgcn_readfirstlane(e >> shift);
-    __syncthreads();
-    // rank by step count, most first, ties in list order
-    const uint32_t key = (uint32_t)its << 6 | (uint32_t)(63 - lane);
-    sc.ent[lane] = key;
-    __syncthreads();
-    int at = 0;
-    {
-      const uint4* k4 = reinterpret_cast<const uint4*>(sc.ent);
-      for (int j = 0; j < (n + 3) >> 2; ++j) {
-        const uint4 q = k4[j];
-        at += (q.x > key ? 1 : 0) + (q.y > key ? 1 : 0) + (q.z > key ? 1 : 0) + (q.w > key ? 1 : 0);
+      const uint32_t id = lane < n ? e >> shift : __builtin_amdgcn_readfirstlane(e >> shift);
+      wave_sync();
+      // rank by step count, most first, ties in list order
+      const uint32_t key = (uint32_t)its << 6 | (uint32_t)(63 - lane);
+      sc.ent[lane] = key;
+      wave_sync();
+      int at = 0;
+      {
+        const uint4* k4 = reinterpret_cast<const uint4*>(sc.ent);
+        for (int j = 0; j < (n + 3) >> 2; ++j) {
+          const uint4 q = k4[j];
+          at += (q.x > key ? 1 : 0) + (q.y > key ? 1 : 0) + (q.z > key ? 1 : 0) + (q.w > key ? 1 : 0);
+        }
       }
+      if (lane >= n) at = lane;  // (padding: keys below every entry's)
+      wave_sync();
+      sc.ent[at] = (uint32_t)packed_box;
+      sc.out[at] = make_uint2(id, row);
     }
-    if (lane >= n) at = lane;  // (padding: keys below every entry's)
     __syncthreads();
-    sc.ent[at] = (uint32_t)packed_box;
-    sc.out[at] = make_uint2(id, row);
-    __syncthreads();
-    for (int g = 0; g < n; g += 4) {
+    for (int g = 4 * wave; g < n; g += 4 * WAVES) {
       const uint32_t bx = sc.ent[g + sub];
       const uint2 out = sc.out[g + sub];
       const int M = __builtin_amdgcn_readfirstlane(bx >> 12);  // the group's first has the most

@@ -6,17 +6,37 @@
 // order a stable LSD radix sort by block id gives the kernel-major pair list.  It is
 // computed as a radix sort whose single digit is the whole block id (2^14 buckets at
 // 2048^2): an atomic histogram of the digit, one exclusive scan of the histogram (which
-// is also the block ranges), a scatter into the buckets, and a per-bucket sort of the
-// kernel ids in LDS that restores the stable order the atomic scatter does not keep.
+// is also the block ranges), a scatter into the buckets, and a per-bucket ranking of the
+// kernel ids that restores the stable order the atomic scatter does not keep.
 // Every pass is integer work over a few MB, so the design minimises launches, not bytes.
 // The fit step uses fixed-width buckets instead (k_scatter_fixed): no histogram and no scan,
 // the bucket of block t is entries [t W, t W + W) of the pair storage.
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace smoe {
 namespace {
 
-// The kernel that group g of a binning kernel's lanes (kPreLanes, kScatterLanes) takes: every
+// Lanes per kernel row (LANES): a group of lanes shares the row's blocks, so that the atomics of
+// one kernel run side by side.  In the kernels whose every lane also works out the row's
+// rectangle (k_preprocess, k_scatter_fixed) sixteen pay while that work does not fill the chip.
+// Measured, 4 / 16 / 64 lanes: fit scatter at 4096 rows 6.4 / 4.8 / 7.4 us, at 65536 rows 11.3 /
+// 13.6 / 45.9; k_preprocess at 3024 rows 7.8 / 6.7 / 11.0, at 65536 rows 12.6 / 21.5 / 70, at 4000
+// rows of 150 blocks each 57 / 37 / 38.  Rows of a few blocks have nothing to share out: four
+// (few_blocks; k_scatter_fixed over 66564 rows of a block each 11.3 against 24.6).  k_scatter
+// reads the rectangle: sixteen always (65536
+// rows 9.6 / 9.5 / 36, a batch of serving requests 108 / 71 / 140, the 4000 wide rows 104 /
+// 53 / 37).
+constexpr int kScatterLanes = 16, kManyKernels = 16384;
+// Calls f(std::integral_constant<int, LANES>) for the kernel rows of S.
+template <class F>
+inline void with_lanes(const Segs& S, F&& f) {
+  if (S.K > kManyKernels || few_blocks(S)) f(std::integral_constant<int, 4>{});
+  else f(std::integral_constant<int, 16>{});
+}
+
+// The kernel that group g of a binning kernel's lanes takes: every
 // 8th of 128 consecutive kernel ids (a bijection on each complete run of 128; the ids past
 // the last one keep their order).  Neighbouring ids are neighbours in the image (the grid
 // initialisation's order, which the kernels keep as they move), so a wave's counter and
@@ -28,13 +48,12 @@ __device__ __forceinline__ int binning_kernel(int g, int K) {
   return (g | 127) < K ? (g & ~127) + ((g & 15) << 3) + ((g >> 4) & 7) : g;
 }
 
-// Four lanes per kernel row (so that a wave covers 16 kernels and a launch has four times the
-// waves to hide its loads): every lane of the quad reads the row and computes the
-// output-block and native-block rectangles; lane 0 writes them and the count, lane q the
-// q-th float4 of the render record, and (tile_counts not null) lane q adds one to the counts
-// of the kernel's covered blocks q, q + 4, ... (row-major).  A row with a NaN or infinite
-// parameter covers no block (it takes part nowhere) and sets the non-finite status word.
-constexpr int kPreLanes = 4;
+// Every lane of a kernel's group reads the row and computes the output-block and native-block
+// rectangles; lane 0 writes them and the count, lane q the q-th float4 of the render record,
+// and (tile_counts not null) lane q adds one to the counts of the kernel's covered blocks q, q +
+// LANES, ... (row-major).  A row with a NaN or infinite parameter covers no block (it takes
+// part nowhere) and sets the non-finite status word.
+template <int LANES>
 __global__ __launch_bounds__(256) void k_preprocess(int C, int order,
                                                     const float* __restrict__ params, Segs S,
                                                     int4* __restrict__ tile_rects,
@@ -44,7 +63,7 @@ __global__ __launch_bounds__(256) void k_preprocess(int C, int order,
                                                     int32_t* __restrict__ tile_counts,
                                                     int32_t* __restrict__ status) {
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-  const int g = gid / kPreLanes, lq = gid % kPreLanes;
+  const int g = gid / LANES, lq = gid % LANES;
   if (g >= S.K) return;
   const int j = binning_kernel(g, S.K);
   const SegGrid sg = seg_of_kernel(S, j);
@@ -73,7 +92,7 @@ __global__ __launch_bounds__(256) void k_preprocess(int C, int order,
     if (!finite) status[kNonfinite] = 1;
   }
   if (lq < rs / 4) write_record_quad(records + (size_t)j * rs, p, ne, lq, l11, l21, l22);
-  if (tile_counts) count_blocks(rc, sg, tile_counts, lq, kPreLanes);
+  if (tile_counts) count_blocks(rc, sg, tile_counts, lq, LANES);
 }
 
 // Exclusive scan of the per-block counts into [begin, end) ranges, with P, the overflow flag
@@ -191,30 +210,40 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(int T, const int32_t* __r
   }
 }
 
-// Four lanes per kernel: lane q appends the kernel id to the buckets of the kernel's
-// covered blocks q, q + 4, ... (row-major inside its block rectangle), so the cursor
-// atomics of one kernel run in parallel rather than one after another.
-constexpr int kScatterLanes = 4;
+// Lane q of a kernel's group appends the kernel id to the buckets of the kernel's covered
+// blocks q, q + 16, ... (row-major inside its block rectangle).  A lane's appends go out four at
+// a time: each waits for its atomic's result only when all four are on their way.
 __global__ __launch_bounds__(256) void k_scatter(Segs S, const int4* __restrict__ tile_rects,
                                                  const int2* __restrict__ ranges,
                                                  int32_t* __restrict__ cursors,
                                                  uint32_t* __restrict__ vals,
                                                  const int32_t* __restrict__ status) {
+  constexpr int AHEAD = 4;
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   const int g = gid / kScatterLanes, q0 = gid % kScatterLanes;
   if (g >= S.K || status[1] != 0) return;
   const int j = binning_kernel(g, S.K);
   const int4 rc = tile_rects[j];
   const int n = rect_count(rc);
-  if (n == 0) return;
+  if (q0 >= n) return;
   const SegGrid sg = seg_of_kernel(S, j);
   const int w = rc.z - rc.x + 1;
-  for (int q = q0; q < n; q += kScatterLanes) {
-    const int t = sg.tile_offset + (rc.y + q / w) * sg.ntx + rc.x + q % w;
-    // the block's count runs down to zero
-    const int pos = atomicSub(&cursors[t], 1) - 1;
-    const int2 rg = ranges[t];
-    if (pos >= 0 && rg.x + pos < rg.y) vals[rg.x + pos] = (uint32_t)j;
+  for (int q = q0; q < n; q += AHEAD * kScatterLanes) {
+    int pos[AHEAD];
+    int2 rg[AHEAD];
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) {
+      const int p = q + k * kScatterLanes;
+      if (p < n) {
+        const int t = sg.tile_offset + (rc.y + p / w) * sg.ntx + rc.x + p % w;
+        pos[k] = atomicSub(&cursors[t], 1) - 1;  // the block's count runs down to zero
+        rg[k] = ranges[t];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k)
+      if (q + k * kScatterLanes < n && pos[k] >= 0 && rg[k].x + pos[k] < rg[k].y)
+        vals[rg[k].x + pos[k]] = (uint32_t)j;
   }
 }
 
@@ -230,6 +259,7 @@ __global__ __launch_bounds__(256) void k_scatter(Segs S, const int4* __restrict_
 // block) and is stored with its count for the step's Adam kernel, which gathers the
 // kernel's partial rows over it.  Thread 0 copies the step counter into the status words
 // and writes the step's Adam scalars, for the step's later kernels.
+template <int LANES>
 __global__ __launch_bounds__(256) void k_scatter_fixed(Segs S, const float* __restrict__ model,
                                                        int np, int4* __restrict__ tile_rects,
                                                        int32_t* __restrict__ counts,
@@ -245,21 +275,20 @@ __global__ __launch_bounds__(256) void k_scatter_fixed(Segs S, const float* __re
     status[kStepShadow] = t0;
     adam_step_scalars(adam, t0, scalars);
   }
-  const int g = gid / kScatterLanes, q0 = gid % kScatterLanes;
-  if (g >= S.K) return;  // (whole groups of kScatterLanes lanes: the shuffles stay inside one)
+  const int g = gid / LANES, q0 = gid % LANES;
+  if (g >= S.K) return;  // (whole groups of LANES lanes: the shuffles stay inside one)
   const int j = binning_kernel(g, S.K);
   const SegGrid sg = seg_of_kernel(S, j);
   // every lane of the kernel's group reads the geometry; lane q0 also checks parameters
-  // 5 + q0, 5 + q0 + kScatterLanes, ... for finiteness
+  // 5 + q0, 5 + q0 + LANES, ... for finiteness
   const float* p = model + (size_t)j * np;
   const float mux = p[0], muy = p[1], l11 = p[2], l21 = p[3], l22 = p[4];
   bool finite = __builtin_isfinite(mux) && __builtin_isfinite(muy) && __builtin_isfinite(l11) &&
                 __builtin_isfinite(l21) && __builtin_isfinite(l22);
-  for (int k = 5 + q0; k < np; k += kScatterLanes) finite = finite && __builtin_isfinite(p[k]);
+  for (int k = 5 + q0; k < np; k += LANES) finite = finite && __builtin_isfinite(p[k]);
   int bad = finite ? 0 : 1;
-  static_assert(kScatterLanes == 4, "the finiteness vote spans a quad");
-  bad |= __shfl_xor(bad, 1);
-  bad |= __shfl_xor(bad, 2);
+#pragma unroll
+  for (int off = 1; off < LANES; off <<= 1) bad |= __shfl_xor(bad, off);
   int4 rc = make_int4(0, 0, -1, -1);
   if (!bad) rc = kernel_rects(mux, muy, l11, l21, l22, sg, S.r, S.box, S.trunc).tile;
   const int n = rect_count(rc);
@@ -269,7 +298,7 @@ __global__ __launch_bounds__(256) void k_scatter_fixed(Segs S, const float* __re
   }
   if (n == 0) return;
   const int w = rc.z - rc.x + 1;
-  for (int q = q0; q < n; q += kScatterLanes) {
+  for (int q = q0; q < n; q += LANES) {
     const int t = sg.tile_offset + (rc.y + q / w) * sg.ntx + rc.x + q % w;
     const int pos = atomicAdd(&cursors[t], 1);
     if (pos < width) {
@@ -281,23 +310,32 @@ __global__ __launch_bounds__(256) void k_scatter_fixed(Segs S, const float* __re
   }
 }
 
-// One wave per block: sort the bucket ascending, write the block-id keys, reset the
-// block's cursor.
-constexpr int kSortRun = 2048;
-__global__ __launch_bounds__(64) void k_sort_buckets(const int2* __restrict__ ranges,
-                                                     uint32_t* __restrict__ vals,
-                                                     uint32_t* __restrict__ vals_alt,
-                                                     uint32_t* __restrict__ keys,
-                                                     int32_t* __restrict__ cursors) {
-  __shared__ uint32_t s[kSortRun];
-  const int t = blockIdx.x;
-  const int2 rg = ranges[t];
-  const int n = rg.y - rg.x;
-  if (threadIdx.x == 0) cursors[t] = 0;
-  if (n <= 0) return;
-  for (int i = threadIdx.x; i < n; i += 64) keys[rg.x + i] = (uint32_t)t;
-  if (n <= 64) rank_sort64(vals + rg.x, n, s, nullptr);
-  else sort_bucket(vals + rg.x, vals_alt + rg.x, n, s, kSortRun);
+// Orders every block's list by kernel id, writes the block-id keys and clears the block's
+// counter.  A wave per block ranks a list of up to 64 ids in registers; a longer one is then
+// taken by the workgroup's four waves together (sort_long).
+constexpr int kSortBlocks = 4;
+__global__ __launch_bounds__(64 * kSortBlocks) void k_sort_buckets(int T,
+                                                                   const int2* __restrict__ ranges,
+                                                                   uint32_t* __restrict__ vals,
+                                                                   uint32_t* __restrict__ vals_alt,
+                                                                   uint32_t* __restrict__ keys,
+                                                                   int32_t* __restrict__ cursors) {
+  __shared__ __align__(16) uint32_t s_rank[kSortBlocks][64];
+  __shared__ LongSortScratch<kSortBlocks, 32768> s_long;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int t0 = blockIdx.x * kSortBlocks, t = t0 + wave;
+  if (t < T) {
+    const int2 rg = ranges[t];
+    const int n = rg.y - rg.x;
+    if (lane == 0) cursors[t] = 0;
+    for (int i = lane; i < n; i += 64) keys[rg.x + i] = (uint32_t)t;
+    if (n > 0 && n <= 64) rank_sort64(vals + rg.x, n, s_rank[wave], nullptr);
+  }
+  for (int k = 0; k < kSortBlocks && t0 + k < T; ++k) {
+    const int2 rg = ranges[t0 + k];
+    if (rg.y - rg.x > 64)
+      sort_long(vals + rg.x, vals_alt + rg.x, rg.y - rg.x, 0, s_long);
+  }
 }
 
 __global__ void k_fill_i32(int32_t* __restrict__ p, int n, int32_t v) {
@@ -319,6 +357,17 @@ __global__ void k_copy_i32(const int32_t* __restrict__ src, int32_t* __restrict_
 
 inline int cdiv(long long a, int b) { return (int)((a + b - 1) / b); }
 
+void preprocess(int C, int order, const float* params, const Segs& S, const smoe_bins& b,
+                int32_t* tile_counts, hipStream_t s) {
+  with_lanes(S, [&](auto lanes) {
+    constexpr int L = decltype(lanes)::value;
+    k_preprocess<L><<<cdiv((long long)S.K * L, 256), 256, 0, s>>>(
+        C, order, params, S, reinterpret_cast<int4*>(b.tile_rects),
+        reinterpret_cast<int4*>(b.native_rects), b.counts, b.records, b.record_stride, tile_counts,
+        b.status);
+  });
+}
+
 }  // namespace
 
 hipError_t launch_count(int C, int order, const float* params, const Segs& S,
@@ -327,11 +376,7 @@ hipError_t launch_count(int C, int order, const float* params, const Segs& S,
   // node, so that the step can be captured into a graph).
   k_fill_counts<<<cdiv(S.T, 256), 256, 0, s>>>(b.tile_counts, S.T, b.status);
   if (S.K > 0) {
-    k_preprocess<<<cdiv((long long)S.K * kPreLanes, 256), 256, 0, s>>>(C, order, params, S,
-                                                 reinterpret_cast<int4*>(b.tile_rects),
-                                                 reinterpret_cast<int4*>(b.native_rects), b.counts,
-                                                 b.records, b.record_stride, b.tile_counts,
-                                                 b.status);
+    preprocess(C, order, params, S, b, b.tile_counts, s);
   }
   return hipGetLastError();
 }
@@ -356,10 +401,7 @@ hipError_t launch_prepare_fit(int C, int order, const float* params, const Segs&
   // overflow flags and the non-finite flag), whatever the workspace held before.
   k_fill_i32<<<1, 64, 0, s>>>(b.status, 8, 0);
   if (S.K > 0) {
-    k_preprocess<<<cdiv((long long)S.K * kPreLanes, 256), 256, 0, s>>>(C, order, params, S,
-                                                 reinterpret_cast<int4*>(b.tile_rects),
-                                                 reinterpret_cast<int4*>(b.native_rects), b.counts,
-                                                 b.records, b.record_stride, nullptr, b.status);
+    preprocess(C, order, params, S, b, nullptr, s);
   }
   return hipGetLastError();
 }
@@ -367,9 +409,12 @@ hipError_t launch_prepare_fit(int C, int order, const float* params, const Segs&
 hipError_t launch_scatter_fixed(const Segs& S, const smoe_bins& b, const float* model, int np,
                                 int width, int shift, const int32_t* step,
                                 const smoe_adam_config& adam, float* scalars, hipStream_t s) {
-  k_scatter_fixed<<<max(1, cdiv((long long)S.K * kScatterLanes, 256)), 256, 0, s>>>(
-      S, model, np, reinterpret_cast<int4*>(b.tile_rects), b.counts, b.tile_counts, b.vals,
-      width, shift, b.status, step, adam, scalars);
+  with_lanes(S, [&](auto lanes) {
+    constexpr int L = decltype(lanes)::value;
+    k_scatter_fixed<L><<<max(1, cdiv((long long)S.K * L, 256)), 256, 0, s>>>(
+        S, model, np, reinterpret_cast<int4*>(b.tile_rects), b.counts, b.tile_counts, b.vals,
+        width, shift, b.status, step, adam, scalars);
+  });
   return hipGetLastError();
 }
 
@@ -393,8 +438,8 @@ hipError_t launch_bin(int C, int order, const float* params, const Segs& S, cons
   if (e == hipSuccess) e = launch_scan(S, b, s);
   if (e == hipSuccess) e = launch_scatter(S, b, s);
   if (e != hipSuccess) return e;
-  k_sort_buckets<<<S.T, 64, 0, s>>>(reinterpret_cast<const int2*>(b.ranges), b.vals, b.vals_alt,
-                                    b.keys, b.tile_counts);
+  k_sort_buckets<<<cdiv(S.T, kSortBlocks), 64 * kSortBlocks, 0, s>>>(
+      S.T, reinterpret_cast<const int2*>(b.ranges), b.vals, b.vals_alt, b.keys, b.tile_counts);
   return hipGetLastError();
 }
 

@@ -48,8 +48,11 @@ void k_fit_tile(FitTileArgs a) {
   constexpr int LDS_FLOATS = kChunk * record_stride(C, ORDER);
   static_assert(LDS_FLOATS >= 64, "the rank sort's scratch lives in the record buffer");
   // the forward's records, then the backward's pixel seeds
-  constexpr int LDS_BYTES = max_of(LDS_FLOATS * 4, kTilePixels * (int)sizeof(PixelSeed<C>));
-  __shared__ float4 srec[LDS_BYTES / 16];
+  // (before both, a long bucket's sort)
+  using LongSort = LongSortScratch<WAVES, 8192>;
+  constexpr int LDS_BYTES =
+      max_of(max_of(LDS_FLOATS * 4, kTilePixels * (int)sizeof(PixelSeed<C>)), (int)sizeof(LongSort));
+  __shared__ float4 srec[(LDS_BYTES + 15) / 16];
   __shared__ __align__(16) BackwardScratch sc;  // sc.ent: also the entries of the chunk being staged
   __shared__ float s_err[WAVES == 1 ? 1 : kTilePixels];
   const int tile = xcd_block(blockIdx.x, a.S.T);
@@ -91,14 +94,12 @@ void k_fit_tile(FitTileArgs a) {
   const float inv_n = 1.0f / ((float)sg.W * (float)sg.H * (float)C);
   // Order the bucket (the scatter appended in arbitrary order).  A bucket of one chunk is
   // ranked in registers and kept in LDS for the forward's staging.
-  constexpr int run = LDS_FLOATS >= 1024 ? 1024 : (LDS_FLOATS >= 512 ? 512 : 256);
-  if (wave != 0) {
-    // (the first wave sorts)
-  } else if (rg.y - rg.x <= kChunk) {
-    rank_sort64(a.vals + rg.x, rg.y - rg.x, reinterpret_cast<uint32_t*>(srec), sc.ent);
+  if (rg.y - rg.x <= kChunk) {
+    if (wave == 0)
+      rank_sort64(a.vals + rg.x, rg.y - rg.x, reinterpret_cast<uint32_t*>(srec), sc.ent);
   } else {
-    sort_bucket(a.vals + rg.x, a.vals_alt + rg.x, rg.y - rg.x, reinterpret_cast<uint32_t*>(srec),
-                run);
+    sort_long(a.vals + rg.x, a.vals_alt + rg.x, rg.y - rg.x, a.shift,
+              *reinterpret_cast<LongSort*>(srec));
   }
   __syncthreads();
 
@@ -350,7 +351,7 @@ hipError_t launch_fit_tile(const smoe_fit_state& st, const Segs& S, int width, i
                 b.tile_loss, b.pair_grads};
   with_shape(st.C, st.order, S, [&](auto sh) {
     using T = decltype(sh);
-    if (S.T <= kSplitForward)
+    if (split_blocks(S))
       k_fit_tile<T::C, T::ORDER, T::RBF, T::TRUNC, 4><<<S.T, 4 * kWave, 0, s>>>(a);
     else
       k_fit_tile<T::C, T::ORDER, T::RBF, T::TRUNC, 1><<<S.T, kWave, 0, s>>>(a);

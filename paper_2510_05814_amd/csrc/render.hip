@@ -257,7 +257,7 @@ hipError_t launch_render(int C, int order, const Segs& S, const smoe_bins& b, fl
                b.status};
   with_shape(C, order, S, [&](auto sh) {
     using T = decltype(sh);
-    if (S.T <= kSplitForward)
+    if (split_blocks(S))
       k_render<T::C, T::ORDER, T::RBF, T::TRUNC, 4><<<S.T, 4 * kWave, 0, s>>>(a);
     else
       k_render<T::C, T::ORDER, T::RBF, T::TRUNC, 1><<<S.T, kWave, 0, s>>>(a);

@@ -59,6 +59,10 @@ struct Segs {
   int K;                                 // kernel rows of all segments
 };
 
+// A batch of rasters of a few blocks each (the windows of the multi-model estimator): a kernel
+// covers no more blocks than its raster has, and a block lists no more kernels.
+inline bool few_blocks(const Segs& S) { return S.tab && S.T / S.n < 16; }
+
 // Blocks of a raster: the 16x16 blocks of the output grid of its scale, aligned to
 // multiples of 16 in the output coordinate o + u (so that at scale s a native block, 16 s
 // output pixels, is a whole number of blocks); a window's first and last blocks may be

@@ -53,7 +53,10 @@ constexpr int kStrips = kTilePixels / kWave;   // 16x4 strips of a block (4)
 // 14.3 / 14.2 / 14.1 / 14.6 against 14.2 / 14.3 / 15.7 / 18.3.  The backward alone has no such
 // terms (its groups of entries are dealt out whole): 16.0 us against 13.8 at 1024 blocks, 24.1
 // against 24.0 at 3600, 30.1 against 28.7 at 5184, 37.1 against 37.9 at 7744.
+// Lists of a few entries (few_blocks) give four waves nothing to share: one (a fit of 1392
+// windows of a block each 22.6 us against 23.5).
 constexpr int kSplitForward = 1536, kSplitBackward = 6144;
+inline bool split_blocks(const Segs& S) { return S.T <= kSplitForward && !few_blocks(S); }
 
 // The wave's index in its workgroup, wave-uniform.
 template <int WAVES>

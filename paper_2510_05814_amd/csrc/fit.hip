@@ -257,7 +257,6 @@ void k_adam_fit(AdamFitArgs f) {
     }
   }
 
-  const SegGrid sg = seg_of_kernel(f.S, live ? j : 0);
   float pm = 0.0f;  // materialized value of parameter i after the step
   if (live && skip && i < NP) pm = f.model[e];
   const bool upd = live && !skip && i < NP;
@@ -265,8 +264,7 @@ void k_adam_fit(AdamFitArgs f) {
   // expert slopes are those of the raw row (the render record this step used holds the same
   // numbers).
   const float gi = finish_gradient<C, ORDER, 6>(
-      gather_param_fit<NP>(j, live && !skip, sg, rc, f.S.K, f.ranges, f.vals, f.pair_grads,
-                           f.shift),
+      gather_param_fit<NP>(j, live && !skip, f.S, rc, f.ranges, f.vals, f.pair_grads, f.shift),
       live && !skip, raw0);
   if (upd) {
     const float lr = i < 2 ? lr_mu : (i < 5 ? ad.lr_chol : (i == 5 ? ad.lr_rho : ad.lr_expert));

@@ -103,29 +103,51 @@ __host__ __device__ inline SegGrid seg_grid_of(const smoe_segment& s) {
   return g;
 }
 
+// The last of n segments whose offset (tile_offset or kernel_offset, ascending, the first 0) is
+// at most x, total being the offset past the last.  Each probe is a dependent load from a
+// table of 48-byte rows, so a large batch is first searched by interpolation: the windows of
+// the multi-model estimator have one block and nearly all the same number of kernels each, and
+// two or three probes find what bisection takes fifteen for.  Bisection finishes the rest.
+template <int32_t smoe_segment::* OFFSET>
+__device__ __forceinline__ int find_segment(const smoe_segment* __restrict__ tab, int n, int total,
+                                            int x) {
+  int lo = 0, hi = n - 1;           // the answer lies in [lo, hi]
+  if (n > 64) {
+    int at_lo = 0, at_end = total;  // offsets of lo and of hi + 1
+    for (int probe = 0; probe < 4 && lo < hi; ++probe) {
+      const float f = (float)(x - at_lo) / (float)(at_end - at_lo);
+      const int g = min(hi, lo + (int)(f * (float)(hi - lo + 1)));
+      const int at = g > lo ? tab[g].*OFFSET : at_lo, next = g < hi ? tab[g + 1].*OFFSET : at_end;
+      if (x < at) {
+        hi = g - 1;
+        at_end = at;
+      } else if (x >= next) {
+        lo = g + 1;
+        at_lo = next;
+      } else {
+        return g;
+      }
+    }
+  }
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (tab[mid].*OFFSET <= x) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
 // Segment of global block t: the last segment whose tile_offset <= t.
 __device__ __forceinline__ SegGrid seg_of_tile(const Segs& S, int t) {
   if (!S.tab) return seg_grid_of(S.one);
-  int lo = 0, hi = S.n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (S.tab[mid].tile_offset <= t) lo = mid;
-    else hi = mid - 1;
-  }
-  return seg_grid_of(S.tab[lo]);
+  return seg_grid_of(S.tab[find_segment<&smoe_segment::tile_offset>(S.tab, S.n, S.T, t)]);
 }
 
 // Segment of global kernel row j: the last segment whose kernel_offset <= j (segments
 // without kernels share their offset with the next one and are skipped by "last").
 __device__ __forceinline__ SegGrid seg_of_kernel(const Segs& S, int j) {
   if (!S.tab) return seg_grid_of(S.one);
-  int lo = 0, hi = S.n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (S.tab[mid].kernel_offset <= j) lo = mid;
-    else hi = mid - 1;
-  }
-  return seg_grid_of(S.tab[lo]);
+  return seg_grid_of(S.tab[find_segment<&smoe_segment::kernel_offset>(S.tab, S.n, S.K, j)]);
 }
 
 // Output pixel index -> native sampling coordinate, the exact binary32 sequence of the

@@ -467,8 +467,8 @@ __device__ __forceinline__ float gather_param(int j, bool live, const SegGrid& s
 // (contiguous per kernel); beyond, at row kSlots K + the bucket slot that the entry's low bits
 // hold, found by a search of the block's sorted list.
 template <int NP>
-__device__ __forceinline__ float gather_param_fit(int j, bool live, const SegGrid& sg, int4 rc,
-                                                  int K, const int2* __restrict__ ranges,
+__device__ __forceinline__ float gather_param_fit(int j, bool live, const Segs& S, int4 rc,
+                                                  const int2* __restrict__ ranges,
                                                   const uint32_t* __restrict__ vals,
                                                   const float* __restrict__ pair_grads,
                                                   int shift) {
@@ -482,12 +482,13 @@ __device__ __forceinline__ float gather_param_fit(int j, bool live, const SegGri
     for (int b = threadIdx.x & 15; b < n; b += 16) {
       int p = j * kSlots + b;
       if (b >= kSlots) {
+        const SegGrid sg = seg_of_kernel(S, j);
         const int dy = b / w;
         const int t = sg.tile_offset + (rc.y + dy) * sg.ntx + rc.x + (b - dy * w);
         const int pos = list_position(j, t, ranges, vals, shift);
         if (pos < 0) continue;
         const int low = (int)(vals[pos] & ((1u << shift) - 1u));
-        p = K * kSlots + ranges[t].x + (low - kSlots);
+        p = S.K * kSlots + ranges[t].x + (low - kSlots);
       }
       add_partial_row<NP>(v, pair_grads, p);
     }

@@ -36,31 +36,58 @@ struct FuseAxis {
 };
 
 template <int C>
+struct Pixel {
+  float v[C];
+};
+
+// A thread per output pixel, 64 x 4 of them a workgroup.  Along a row of windows the position of
+// the pixel moves from window to window by the earlier one's size and the change of its row's
+// start: a few 32-bit operations a window.  The loads of AHEAD windows are issued before the
+// first is added (RGB: one 12-byte load a window); the sum keeps its order.  512^2 RGB, 64
+// windows a pixel (204 MB): 76.6 -> 59.9 us against 64-bit positions worked out and three 4-byte
+// loads waited for in every window.
+template <int C>
 __global__ __launch_bounds__(256) void k_fuse_windows(const float* __restrict__ win, FuseAxis ax,
                                                       FuseAxis ay, float hyp,
                                                       float* __restrict__ out) {
+  constexpr int AHEAD = 8;
   const int x = blockIdx.x * 64 + (threadIdx.x & 63);
   const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
   if (x >= ax.n || y >= ay.n) return;
   const long long row_pixels = (long long)ax.m * ax.n;
   const int kx0 = x / ax.d, ky0 = y / ay.d;
+  const long long px0 = ax.prefix(kx0);
   float acc[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) acc[c] = 0.0f;
   for (int ky = ky0; ky < ky0 + ay.m; ++ky) {
-    const long long hy = ay.len(ky);
-    const long long base = ay.prefix(ky) * row_pixels;
-    const long long dy = y - ay.start(ky);
-    for (int kx = kx0; kx < kx0 + ax.m; ++kx) {
-      const long long wx = ax.len(kx);
-      const long long p = base + hy * ax.prefix(kx) + dy * wx + (x - ax.start(kx));
+    const int hy = ay.len(ky), dy = y - ay.start(ky);
+    // the first window's pixels of this row of windows, then offsets from there
+    const Pixel<C>* row = reinterpret_cast<const Pixel<C>*>(win) + ay.prefix(ky) * row_pixels + hy * px0;
+    int before = 0;  // pixels of the windows passed
+    for (int i0 = 0; i0 < ax.m; i0 += AHEAD) {
+      Pixel<C> v[AHEAD];
 #pragma unroll
-      for (int c = 0; c < C; ++c) acc[c] += win[p * C + c];
+      for (int i = 0; i < AHEAD; ++i) {
+        if (i0 + i < ax.m) {
+          const int s = ax.start(kx0 + i0 + i), wx = ax.len(kx0 + i0 + i);
+          v[i] = row[before + dy * wx + (x - s)];
+          before += hy * wx;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {
+        if (i0 + i < ax.m) {
+#pragma unroll
+          for (int c = 0; c < C; ++c) acc[c] += v[i].v[c];
+        }
+      }
     }
   }
-  const long long o = ((long long)y * ax.n + x) * C;
+  Pixel<C> o;
 #pragma unroll
-  for (int c = 0; c < C; ++c) out[o + c] = acc[c] / hyp;
+  for (int c = 0; c < C; ++c) o.v[c] = acc[c] / hyp;
+  reinterpret_cast<Pixel<C>*>(out)[(long long)y * ax.n + x] = o;
 }
 
 }  // namespace

@@ -28,9 +28,16 @@ class SMoERender(torch.autograd.Function):
             raise ValueError("raw must be a cuda float32 [K, NP] tensor")
         grid = core.make_grid(width, height, scale, origin_x, origin_y, radius, mode=mode,
                               trunc=trunc)
-        model = core.materialize(raw.detach().contiguous(), C, order)
-        bins = core.bin(model, C, order, grid)
-        image, denom, _, _ = core.render(model, C, order, grid, bins=bins)
+        st = torch.cuda.current_stream()
+        model = core.materialize(raw.detach().contiguous(), C, order, st)
+        # The render is launched before the host learns whether the pairs fitted (if not, it has
+        # rendered empty lists): one wait, for work that is already on its way.
+        bins = core.bin(model, C, order, grid, stream=st, grow=False)
+        image, denom, _, _ = core.render(model, C, order, grid, bins=bins, stream=st)
+        over, status = bins.read_status(st)
+        if over:
+            bins = core.bin(model, C, order, grid, capacity=core.grown_capacity(status), stream=st)
+            image, denom, _, _ = core.render(model, C, order, grid, bins=bins, stream=st)
         ctx.save_for_backward(model, image, denom)
         ctx.bins, ctx.grid, ctx.C, ctx.order = bins, grid, C, order
         return image

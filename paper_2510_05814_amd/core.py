@@ -149,19 +149,26 @@ def initial_capacity(K: int, T: int) -> int:
     return max(1024, 8 * K + 2 * T)
 
 
+def grown_capacity(status) -> int:
+    """The pair capacity of a re-made workspace after an overflow with these status words."""
+    return int(status[0] * 1.25) + 1024
+
+
 def bin(params: torch.Tensor, C_: int, order: int, grid: C.SmoeGrid, bins: Bins | None = None,
         capacity: int | None = None, stream=None, grow: bool = True) -> Bins:
     """smoe_bin; with grow=True the workspace is re-made until the pairs fit (host sync)."""
     m = model_struct(params, C_, order)
     T = tiles(grid.width, grid.height, grid.origin_x, grid.origin_y)
     if bins is None:
-        bins = Bins(m.K, C_, order, T, capacity or initial_capacity(m.K, T), params.device)
+        # (every word that is read is written first: the storage need not be cleared)
+        bins = Bins(m.K, C_, order, T, capacity or initial_capacity(m.K, T), params.device,
+                    zero=False)
     C.smoe_bin(m, grid, bins.c, _stream(stream))
     if grow:
         over, st = bins.read_status(stream)
         if over:
-            bins = Bins(m.K, C_, order, max(T, bins.max_tiles), int(st[0] * 1.25) + 1024,
-                        params.device)
+            bins = Bins(m.K, C_, order, max(T, bins.max_tiles), grown_capacity(st),
+                        params.device, zero=False)
             C.smoe_bin(m, grid, bins.c, _stream(stream))
     return bins
 
@@ -282,13 +289,13 @@ def bin_batched(params: torch.Tensor, C_: int, order: int, segs: Segments, radiu
                         _trunc(trunc))
     if bins is None:
         bins = Bins(segs.K, C_, order, segs.T, capacity or initial_capacity(segs.K, segs.T),
-                    params.device)
+                    params.device, zero=False)
     C.smoe_bin_batched(batch, bins.c, _stream(stream))
     if grow:
         over, st = bins.read_status(stream)
         if over:
-            bins = Bins(segs.K, C_, order, max(segs.T, bins.max_tiles), int(st[0] * 1.25) + 1024,
-                        params.device)
+            bins = Bins(segs.K, C_, order, max(segs.T, bins.max_tiles), grown_capacity(st),
+                        params.device, zero=False)
             C.smoe_bin_batched(batch, bins.c, _stream(stream))
     return bins
 

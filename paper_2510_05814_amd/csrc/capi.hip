@@ -543,8 +543,9 @@ smoe_status smoe_read_status(const smoe_bins* bins, int32_t* out4, void* stream)
   if (!bins || !bins->status) return SMOE_ERR_INVALID;
   int32_t h[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (hipStreamSynchronize(s) != hipSuccess) return SMOE_ERR_HIP;
-  if (hipMemcpy(h, bins->status, sizeof(h), hipMemcpyDeviceToHost) != hipSuccess)
+  // one copy on the stream, one wait
+  if (hipMemcpyAsync(h, bins->status, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess)
     return SMOE_ERR_HIP;
   // word 3: the last binning's non-finite flag; word 7: the fit's (sticky) one
   h[3] = (h[3] || h[7]) ? 1 : 0;

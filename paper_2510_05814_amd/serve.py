@@ -16,7 +16,9 @@ Two servers share the request format and the report:
   memory (output image + their share of the binning workspace) fits the HBM budget beside
   the batches still in flight, lays them out as segments of one raster table, and issues
   one batched binning and ONE render launch over the concatenated (request, block) list on
-  that stream.  Batches on different streams overlap on the device; finished batches
+  that stream.  Once no request is still to arrive, the next batch is also issued behind one
+  that fills the GPU, to start when that one ends (twelve saturated requests in two batches
+  1341 -> 1234 us).  Batches on different streams overlap on the device; finished batches
   release their memory, stream and blocks, and the queue is admitted again.  Nothing waits
   on the device except to learn which batches have finished.
 * ``PlainServer`` -- the baseline: one bin + render launch sequence per request, in
@@ -193,10 +195,11 @@ def _summary(results, name: str, extra=None):
     t1 = max(r.done for r in results)
     wait = np.array([r.started - r.request.arrival for r in results]) * 1e3
     gpu = np.array([r.done - r.started for r in results]) * 1e3
-    out = {"server": name, "requests": len(results), "p50_ms": float(np.percentile(lat, 50)),
-           "p99_ms": float(np.percentile(lat, 99)), "mean_ms": float(lat.mean()),
-           "wait_p50_ms": float(np.percentile(wait, 50)), "wait_p99_ms": float(np.percentile(wait, 99)),
-           "gpu_p50_ms": float(np.percentile(gpu, 50)), "gpu_p99_ms": float(np.percentile(gpu, 99)),
+    (p50, w50, g50), (p99, w99, g99) = np.percentile(np.stack([lat, wait, gpu]), [50, 99],
+                                                     axis=1).tolist()
+    out = {"server": name, "requests": len(results), "p50_ms": p50, "p99_ms": p99,
+           "mean_ms": float(lat.mean()), "wait_p50_ms": w50, "wait_p99_ms": w99,
+           "gpu_p50_ms": g50, "gpu_p99_ms": g99,
            "max_ms": float(lat.max()), "pixels": int(px), "makespan_s": float(t1 - t0),
            "pixels_per_s": float(px / max(t1 - t0, 1e-9)),
            "requests_per_s": float(len(results) / max(t1 - t0, 1e-9))}
@@ -238,6 +241,7 @@ class _Hip:
             L.hipEventQuery.argtypes = [vp]
             L.hipEventSynchronize.argtypes = [vp]
             L.hipEventElapsedTime.argtypes = [ct.POINTER(ct.c_float), vp, vp]
+            L.hipStreamWaitEvent.argtypes = [vp, vp, ct.c_uint]
             L.hipMemcpyAsync.argtypes = [vp, vp, ct.c_size_t, ct.c_int, vp]
             _Hip._lib = L
         self.L = _Hip._lib
@@ -258,6 +262,10 @@ class _Hip:
     def sync(self, ev: int):
         if self.L.hipEventSynchronize(ev) != 0:
             raise RuntimeError("hipEventSynchronize failed")
+
+    def wait(self, stream: int, ev: int):
+        if self.L.hipStreamWaitEvent(stream, ev, 0) != 0:
+            raise RuntimeError("hipStreamWaitEvent failed")
 
     def elapsed_s(self, a: int, b: int) -> float:
         f = ct.c_float()
@@ -433,13 +441,17 @@ class Server:
         ws = C.smoe_render_workspace_bytes(K, self.bank.C, self.bank.order, T, P)
         return ws + px * self.nbytes_px + 64 * len(reqs), K, T, P
 
-    def _launch(self, batch: _Batch, keep_outputs: bool, K: int, T: int, P: int):
+    def _launch(self, batch: _Batch, keep_outputs: bool, K: int, T: int, P: int,
+                after: _Batch | None = None):
+        """after: a batch in flight that this one runs behind (on the device)."""
         b = self.bank
         sl = self.slots[batch.slot]
         st = sl.stream
         dev = b.params.device
         hip = self.hip
         with torch.cuda.stream(st):
+            if after is not None:
+                hip.wait(st.cuda_stream, after.done)
             batch.start = sl.start
             hip.record(batch.start, st.cuda_stream)
             bins = sl.layout(K, b.C, b.order, T, P)
@@ -534,8 +546,17 @@ class Server:
                     sl.batch = None
                     free.append(si)
                     inflight -= 1
-            while (free and pending and inflight_blocks < self.fill_blocks
-                   and (not inflight or len(pending) >= self.overlap_backlog)):
+            # Once every request has arrived, waiting for a batch that fills the GPU gains no
+            # company: the next one is issued behind it, so that the device goes from one to
+            # the other without the host in between.
+            last = nxt == len(order)
+            while free and pending and (
+                    (inflight_blocks < self.fill_blocks
+                     and (not inflight or len(pending) >= self.overlap_backlog))
+                    or (last and inflight == 1)):
+                after = None
+                if inflight_blocks >= self.fill_blocks:
+                    after = next(sl.batch for sl in self.slots if sl.batch is not None)
                 if len(pending) == 1:  # the common case at low load
                     k, t, p, _, need = pending[0]._smoe_info
                     if in_use + need > self.budget:
@@ -557,7 +578,7 @@ class Server:
                 free.remove(si)
                 bt = _Batch(nb, si, got, need, blocks=shape[1])
                 nb += 1
-                self._launch(bt, keep_outputs, *shape)
+                self._launch(bt, keep_outputs, *shape, after=after)
                 self.slots[si].batch = bt
                 inflight += 1
                 inflight_blocks += bt.blocks

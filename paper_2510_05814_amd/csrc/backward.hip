@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kWave * WAVES) void k_backward(BackwardArgs a) {
   const float2 o = block_base(sg, tile - sg.tile_offset);
   backward_accumulate<C, ORDER, false, WAVES>(block_box(sg, tile - sg.tile_offset), o.x, o.y, sg.inv_s,
                                        a.S.r, a.S.r2, a.records, a.vals, 0, false, a.ranges[tile],
-                                       seeds, sc, false, a.pair_grads);
+                                       seeds, sc, false, nullptr, a.pair_grads);
 }
 
 struct GatherArgs {

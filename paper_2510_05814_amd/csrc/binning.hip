@@ -257,8 +257,9 @@ __global__ __launch_bounds__(256) void k_scatter(Segs S, const int4* __restrict_
 // (the fused render resets them).  The kernel's block rectangle comes from its model row
 // (kernel_rects, the binning's own rule; a row with a NaN or infinite parameter covers no
 // block) and is stored with its count for the step's Adam kernel, which gathers the
-// kernel's partial rows over it.  Thread 0 copies the step counter into the status words
-// and writes the step's Adam scalars, for the step's later kernels.
+// kernel's partial rows over it.  The last workgroup copies the step counter into the status
+// words and writes the step's Adam scalars, for the step's later kernels (three powf, which
+// the first kernels' appends would wait for in their wave).
 template <int LANES>
 __global__ __launch_bounds__(256) void k_scatter_fixed(Segs S, const float* __restrict__ model,
                                                        int np, int4* __restrict__ tile_rects,
@@ -271,9 +272,12 @@ __global__ __launch_bounds__(256) void k_scatter_fixed(Segs S, const float* __re
                                                        float* __restrict__ scalars) {
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   const int t0 = step[0];
-  if (gid == 0) {
-    status[kStepShadow] = t0;
-    adam_step_scalars(adam, t0, scalars);
+  if (blockIdx.x == gridDim.x - 1) {
+    if (threadIdx.x == 0) {
+      status[kStepShadow] = t0;
+      adam_step_scalars(adam, t0, scalars);
+    }
+    return;
   }
   const int g = gid / LANES, q0 = gid % LANES;
   if (g >= S.K) return;  // (whole groups of LANES lanes: the shuffles stay inside one)
@@ -329,7 +333,7 @@ __global__ __launch_bounds__(64 * kSortBlocks) void k_sort_buckets(int T,
     const int n = rg.y - rg.x;
     if (lane == 0) cursors[t] = 0;
     for (int i = lane; i < n; i += 64) keys[rg.x + i] = (uint32_t)t;
-    if (n > 0 && n <= 64) rank_sort64(vals + rg.x, n, s_rank[wave], nullptr);
+    if (n > 0 && n <= 64) rank_sort64(vals + rg.x, n, s_rank[wave]);
   }
   for (int k = 0; k < kSortBlocks && t0 + k < T; ++k) {
     const int2 rg = ranges[t0 + k];
@@ -338,9 +342,12 @@ __global__ __launch_bounds__(64 * kSortBlocks) void k_sort_buckets(int T,
   }
 }
 
-__global__ void k_fill_i32(int32_t* __restrict__ p, int n, int32_t v) {
+// A fit's first kernel: zero the bucket cursors and the status words (P, overflow, longest list,
+// step shadow, the overflow flags and the non-finite flag), whatever the workspace held before.
+__global__ void k_prepare_fit(int32_t* __restrict__ cursors, int n, int32_t* __restrict__ status) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+  if (i < n) cursors[i] = 0;
+  if (i < 8) status[i] = 0;
 }
 
 // The binning's first kernel: zero the per-block counters and the non-finite flag.
@@ -396,10 +403,7 @@ hipError_t launch_scan(const Segs& S, const smoe_bins& b, hipStream_t s) {
 
 hipError_t launch_prepare_fit(int C, int order, const float* params, const Segs& S,
                               const smoe_bins& b, hipStream_t s) {
-  k_fill_i32<<<cdiv(S.T, 256), 256, 0, s>>>(b.tile_counts, S.T, 0);
-  // A fresh fit starts from clear status words (P, overflow, longest list, step shadow, the
-  // overflow flags and the non-finite flag), whatever the workspace held before.
-  k_fill_i32<<<1, 64, 0, s>>>(b.status, 8, 0);
+  k_prepare_fit<<<cdiv(S.T, 256), 256, 0, s>>>(b.tile_counts, S.T, b.status);
   if (S.K > 0) {
     preprocess(C, order, params, S, b, nullptr, s);
   }
@@ -411,7 +415,7 @@ hipError_t launch_scatter_fixed(const Segs& S, const smoe_bins& b, const float* 
                                 const smoe_adam_config& adam, float* scalars, hipStream_t s) {
   with_lanes(S, [&](auto lanes) {
     constexpr int L = decltype(lanes)::value;
-    k_scatter_fixed<L><<<max(1, cdiv((long long)S.K * L, 256)), 256, 0, s>>>(
+    k_scatter_fixed<L><<<cdiv((long long)S.K * L, 256) + 1, 256, 0, s>>>(
         S, model, np, reinterpret_cast<int4*>(b.tile_rects), b.counts, b.tile_counts, b.vals,
         width, shift, b.status, step, adam, scalars);
   });

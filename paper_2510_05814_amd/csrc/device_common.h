@@ -158,16 +158,11 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Sorts a bucket of n <= 64 distinct entries seg[0, n) ascending with one wave: each lane
-// takes one entry, counts the bucket's entries below it (its rank) from broadcast reads of
-// the whole bucket in LDS, and stores it at its rank, into `out` (LDS, kept for the caller)
-// (if not null) and back into seg.  scratch: 64 u32 of LDS.
-__device__ __forceinline__ void rank_sort64(uint32_t* __restrict__ seg, int n,
-                                            uint32_t* __restrict__ scratch,
-                                            uint32_t* __restrict__ out) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t e = lane < n ? seg[lane] : 0xFFFFFFFFu;
-  scratch[lane] = e;  // padding above n: no entry is greater
+// The rank of a lane's entry e among the n <= 64 distinct ones of a wave (e of lanes 0 .. n - 1;
+// the others pass 0xFFFFFFFF): the number of entries below it, from broadcast reads of all of
+// them in LDS.  scratch: 64 u32 of LDS, 16-byte aligned.
+__device__ __forceinline__ int rank64(uint32_t e, int n, uint32_t* __restrict__ scratch) {
+  scratch[threadIdx.x & 63] = e;
   wave_sync();
   int rank = 0;
   const uint4* s4 = reinterpret_cast<const uint4*>(scratch);
@@ -175,12 +170,17 @@ __device__ __forceinline__ void rank_sort64(uint32_t* __restrict__ seg, int n,
     const uint4 q = s4[j];
     rank += (q.x < e ? 1 : 0) + (q.y < e ? 1 : 0) + (q.z < e ? 1 : 0) + (q.w < e ? 1 : 0);
   }
-  if (lane < n) {
-    if (out) out[rank] = e;
-    seg[rank] = e;
-  }
-  __threadfence_block();
   wave_sync();
+  return rank;
+}
+
+// Sorts a list of n <= 64 distinct entries seg[0, n) ascending with one wave.
+__device__ __forceinline__ void rank_sort64(uint32_t* __restrict__ seg, int n,
+                                            uint32_t* __restrict__ scratch) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t e = lane < n ? seg[lane] : 0xFFFFFFFFu;
+  const int rank = rank64(e, n, scratch);
+  if (lane < n) seg[rank] = e;
 }
 
 // Scratch of sort_long: a bitmap over a window of kernel ids and, per word, the ids below it.

@@ -47,11 +47,15 @@ void k_fit_tile(FitTileArgs a) {
   constexpr int ROWS = kStrips / WAVES;
   constexpr int LDS_FLOATS = kChunk * record_stride(C, ORDER);
   static_assert(LDS_FLOATS >= 64, "the rank sort's scratch lives in the record buffer");
-  // the forward's records, then the backward's pixel seeds
-  // (before both, a long bucket's sort)
+  // The forward's records and the backward's pixel seeds: the one after the other in the same
+  // place, so that eight one-wave blocks fit a SIMD's share of LDS; side by side with several
+  // waves to a block, where the backward then reads its records from LDS.  (Before both, a
+  // long bucket's sort.)
   using LongSort = LongSortScratch<WAVES, 8192>;
+  constexpr int REC_BYTES = LDS_FLOATS * 4, SEED_BYTES = kTilePixels * (int)sizeof(PixelSeed<C>);
+  constexpr int SEED_AT = WAVES == 1 ? 0 : REC_BYTES;
   constexpr int LDS_BYTES =
-      max_of(max_of(LDS_FLOATS * 4, kTilePixels * (int)sizeof(PixelSeed<C>)), (int)sizeof(LongSort));
+      max_of(max_of(REC_BYTES, SEED_AT + SEED_BYTES), (int)sizeof(LongSort));
   __shared__ float4 srec[(LDS_BYTES + 15) / 16];
   __shared__ __align__(16) BackwardScratch sc;  // sc.ent: also the entries of the chunk being staged
   __shared__ float s_err[WAVES == 1 ? 1 : kTilePixels];
@@ -92,34 +96,64 @@ void k_fit_tile(FitTileArgs a) {
   // divided by W H C, so that the sum over all blocks is the sum of the rasters' MSEs.
   const float inv_n2 = 2.0f / ((float)sg.W * (float)sg.H * (float)C);
   const float inv_n = 1.0f / ((float)sg.W * (float)sg.H * (float)C);
-  // Order the bucket (the scatter appended in arbitrary order).  A bucket of one chunk is
-  // ranked in registers and kept in LDS for the forward's staging.
-  if (rg.y - rg.x <= kChunk) {
-    if (wave == 0)
-      rank_sort64(a.vals + rg.x, rg.y - rg.x, reinterpret_cast<uint32_t*>(srec), sc.ent);
+  const BlockBox bb = block_box(sg, tile - sg.tile_offset);
+  // Order the bucket (the scatter appended in arbitrary order).  A list of one chunk: a lane per
+  // entry ranks it in registers while its record is on its way from memory, and writes the
+  // record to its place for the forward; the backward's layout is worked out from the same
+  // record, by the second wave if there is one.  The ordered entries go back for Adam's gather,
+  // once every wave has read them.
+  const int lane = threadIdx.x & 63;
+  const int n = __builtin_amdgcn_readfirstlane(cnt);
+  const bool one_chunk = n <= kChunk;
+  if (one_chunk) {
+    constexpr int RS = record_stride(C, ORDER), Q = RS / 4;
+    uint32_t e = 0xFFFFFFFFu;
+    int rank = 0;
+    if (n > 0 && wave < 2) {
+      float r[RS] = {};
+      if (lane < n) {
+        e = a.vals[rg.x + lane];
+        load_record<RS>(r, reinterpret_cast<const float4*>(a.records + (size_t)(e >> a.shift) * RS));
+      }
+      rank = rank64(e, n, WAVES > 1 && wave == 0 ? reinterpret_cast<uint32_t*>(srec)
+                                                 : reinterpret_cast<uint32_t*>(sc.out));
+      if (wave == 0 && lane < n) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+          srec[rank * Q + q] = make_float4(r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]);
+      }
+      if (wave == (WAVES > 1 ? 1 : 0))
+        lay_out_entries(bb, a.S.r, n, make_float4(r[0], r[1], r[2], r[3]), r[4], WAVES > 1 ? (uint32_t)rank : e >> a.shift,
+                        partial_row(e, a.shift, true, 0, a.S.K, rg.x), sc);
+    }
+    __syncthreads();
+    if (wave == 0 && lane < n) a.vals[rg.x + rank] = e;
   } else {
-    sort_long(a.vals + rg.x, a.vals_alt + rg.x, rg.y - rg.x, a.shift,
-              *reinterpret_cast<LongSort*>(srec));
+    sort_long(a.vals + rg.x, a.vals_alt + rg.x, n, a.shift, *reinterpret_cast<LongSort*>(srec));
   }
-  __syncthreads();
 
   const PixelCoords<ROWS> px = lane_pixels<WAVES>(sg, tile - sg.tile_offset);
-  float D[ROWS], N[ROWS][C];
-  const BlockBox bb = block_box(sg, tile - sg.tile_offset);
-  forward_accumulate<C, ORDER, TRUNC, WAVES>(px, bb, a.S.r2, a.S.cut_scale, a.S.cut_offset, a.records,
-                                      a.vals, a.shift, rg, srec, D, N, sc.ent);
-
-  const int lane = threadIdx.x & 63;
-  PixelSeed<C>* seeds = reinterpret_cast<PixelSeed<C>*>(srec);
-  __syncthreads();  // the records are read: their place takes the seeds
   const BlockPixels bp = block_pixels<WAVES>(sg, tile - sg.tile_offset);
   const PixelValue<C>* tgt = reinterpret_cast<const PixelValue<C>*>(a.target) + bp.base;
   bool in[ROWS];
   PixelValue<C> t[ROWS], y[ROWS];
+  auto load_target = [&]() {
 #pragma unroll
-  for (int i = 0; i < ROWS; ++i) {
-    in[i] = in_raster(px.u, px.v0 + 4 * i, sg);
-    if (in[i]) t[i] = tgt[bp.off + i * bp.step];
+    for (int i = 0; i < ROWS; ++i) {
+      in[i] = in_raster(px.u, px.v0 + 4 * i, sg);
+      if (in[i]) t[i] = tgt[bp.off + i * bp.step];
+    }
+  };
+  if (WAVES > 1) load_target();  // on its way while the forward runs
+  float D[ROWS], N[ROWS][C];
+  forward_accumulate<C, ORDER, TRUNC, WAVES>(px, bb, a.S.r2, a.S.cut_scale, a.S.cut_offset,
+                                             a.records, a.vals, a.shift, rg, srec, D, N, sc.ent,
+                                             one_chunk);
+
+  PixelSeed<C>* seeds = reinterpret_cast<PixelSeed<C>*>(reinterpret_cast<char*>(srec) + SEED_AT);
+  if (WAVES == 1) {
+    __syncthreads();  // the records are read: their place takes the seeds
+    load_target();
   }
   float err[ROWS];
 #pragma unroll
@@ -166,9 +200,10 @@ void k_fit_tile(FitTileArgs a) {
 
   // each partial row goes to the row its entry names, where Adam reads it
   const float2 o = block_base(sg, tile - sg.tile_offset);
-  backward_accumulate<C, ORDER, true, WAVES>(bb, o.x, o.y, 1.0f, a.S.r,
-                                      a.S.r2, a.records, a.vals, a.shift, true, rg, seeds, sc, true,
-                                      a.pair_grads, a.S.K);
+  backward_accumulate<C, ORDER, true, WAVES>(bb, o.x, o.y, 1.0f, a.S.r, a.S.r2, a.records, a.vals,
+                                             a.shift, true, rg, seeds, sc, one_chunk,
+                                             WAVES > 1 && one_chunk ? srec : nullptr,
+                                             a.pair_grads, a.S.K);
 }
 
 struct AdamFitArgs {

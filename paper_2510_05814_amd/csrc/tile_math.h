@@ -176,26 +176,35 @@ __device__ __forceinline__ void stage_records(float4* __restrict__ srec,
   __syncthreads();
 }
 
-// The same with the entries in LDS: ent[k] is entry base + k, copied there from vals first
-// unless `ready` (the caller's sort left the list there).
+// The same by way of ent, LDS room for the chunk's entries.
 template <int RS, int WAVES>
 __device__ __forceinline__ void stage_records_lds(float4* __restrict__ srec,
                                                   const float* __restrict__ records,
                                                   const uint32_t* __restrict__ vals, int base,
-                                                  int n, int shift, uint32_t* __restrict__ ent,
-                                                  bool ready) {
+                                                  int n, int shift, uint32_t* __restrict__ ent) {
   constexpr int Q = RS / 4;
   __syncthreads();
-  if (!ready) {
-    const int t = local_thread();
-    if (t < n) ent[t] = vals[base + t];
-    __syncthreads();
-  }
+  const int t = local_thread();
+  if (t < n) ent[t] = vals[base + t];
+  __syncthreads();
   for (int i = local_thread(); i < n * Q; i += kWave * WAVES) {
     const int k = i / Q, c = i - k * Q;
     srec[i] = reinterpret_cast<const float4*>(records + (size_t)(ent[k] >> shift) * RS)[c];
   }
   __syncthreads();
+}
+
+// A render record of RS floats into registers.
+template <int RS>
+__device__ __forceinline__ void load_record(float (&r)[RS], const float4* __restrict__ f4) {
+#pragma unroll
+  for (int k = 0; k < RS / 4; ++k) {
+    const float4 f = f4[k];
+    r[4 * k] = f.x;
+    r[4 * k + 1] = f.y;
+    r[4 * k + 2] = f.z;
+    r[4 * k + 3] = f.w;
+  }
 }
 
 // Entries of a staged chunk for which some pixel of the block may lie beyond the render's
@@ -219,10 +228,10 @@ __device__ __forceinline__ uint64_t far_entries(const BlockBox& bb, const float4
   return __ballot(far);
 }
 
-// One list entry of the forward: adds its terms to D = sum pi K and N_c = sum pi K m_c of
-// the lane's four pixels that the render's rule keeps.  TRUNC == SMOE_TRUNC_RENDER: the
+// One list entry of the forward: its terms pi K (e) and expert values m_c at the lane's pixels,
+// e = 0 where the render's rule drops the term; D = sum pi K, N_c = sum pi K m_c.  TRUNC == SMOE_TRUNC_RENDER: the
 // ellipse q <= r^2.  TRUNC == SMOE_TRUNC_GRADIENT (the block lists decide the render): every
-// term binary32 holds, i.e. whose exponent a = rho log2(e) - q log2(e)/2 is >= -125.  f4: the
+// term binary32 holds, i.e. whose exponent a = rho log2(e) - q log2(e)/2 is >= -125.  r: the
 // entry's render record; cut_scale, cut_offset: the render's bound in the compare-free form of
 // Segs; far: whether some pixel of the block may lie beyond that bound.
 //
@@ -239,19 +248,10 @@ __device__ __forceinline__ uint64_t far_entries(const BlockBox& bb, const float4
 // Measured: binning and render of a 2048^2 model with 65536 kernels 88.5 -> 83.7 us, its fit
 // step 116.1 -> 114.6 us, a 512^2 render with lists of several hundred 332 -> 320 us.
 template <int C, int ORDER, int TRUNC, int ROWS>
-__device__ __forceinline__ void forward_entry(const PixelCoords<ROWS>& px, float r2, float cut_scale,
-                                              float cut_offset, const float4* f4, bool far,
-                                              float (&D)[ROWS], float (&N)[ROWS][C]) {
-  constexpr int RS = record_stride(C, ORDER);
-  float r[RS];
-#pragma unroll
-  for (int k = 0; k < RS / 4; ++k) {
-    const float4 f = f4[k];
-    r[4 * k] = f.x;
-    r[4 * k + 1] = f.y;
-    r[4 * k + 2] = f.z;
-    r[4 * k + 3] = f.w;
-  }
+__device__ __forceinline__ void entry_terms(const PixelCoords<ROWS>& px, float r2, float cut_scale,
+                                            float cut_offset,
+                                            const float (&r)[record_stride(C, ORDER)], bool far,
+                                            float (&e)[ROWS], float (&m)[ROWS][C]) {
   const float dx = px.x - r[0];
   const float z1 = dx * r[2];
   const float tt = r[3] * z1;
@@ -284,10 +284,16 @@ __device__ __forceinline__ void forward_entry(const PixelCoords<ROWS>& px, float
       q[i] = zz1 + z2 * z2;
     }
     if (TRUNC == SMOE_TRUNC_RENDER) {
-      float qmax = q[0];
+      // (the bound is the identity, bit for bit, where every pixel lies inside: four pixels a
+      // lane ask first, one applies it)
+      bool out = ROWS == 1;
+      if (ROWS > 1) {
+        float qmax = q[0];
 #pragma unroll
-      for (int i = 1; i < ROWS; ++i) qmax = __builtin_fmaxf(qmax, q[i]);
-      if (__any(!(qmax <= r2))) {
+        for (int i = 1; i < ROWS; ++i) qmax = __builtin_fmaxf(qmax, q[i]);
+        out = __any(!(qmax <= r2));
+      }
+      if (out) {
 #pragma unroll
         for (int i = 0; i < ROWS; ++i)
           q[i] = __builtin_fmaxf(q[i], __builtin_fmaf(q[i], cut_scale, cut_offset));
@@ -304,14 +310,22 @@ __device__ __forceinline__ void forward_entry(const PixelCoords<ROWS>& px, float
   }
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) {
-    const float e = __builtin_amdgcn_exp2f(a[i]);
-    D[i] += e;
+    e[i] = __builtin_amdgcn_exp2f(a[i]);
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      float m = mx[c];
-      if (ORDER == 1) m = __builtin_fmaf(r[kRecExpert + 2 * C + c], dy[i], m);
-      N[i][c] = __builtin_fmaf(e, m, N[i][c]);
-    }
+    for (int c = 0; c < C; ++c)
+      m[i][c] = ORDER == 1 ? __builtin_fmaf(r[kRecExpert + 2 * C + c], dy[i], mx[c]) : mx[c];
+  }
+}
+
+// The terms of one entry added to the pixels' sums.
+template <int C, int ROWS>
+__device__ __forceinline__ void add_terms(const float (&e)[ROWS], const float (&m)[ROWS][C],
+                                          float (&D)[ROWS], float (&N)[ROWS][C]) {
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) {
+    D[i] += e[i];
+#pragma unroll
+    for (int c = 0; c < C; ++c) N[i][c] = __builtin_fmaf(e[i], m[i][c], N[i][c]);
   }
 }
 
@@ -324,13 +338,37 @@ __device__ __forceinline__ void forward_chunk(const PixelCoords<ROWS>& px, const
   constexpr int RS = record_stride(C, ORDER);
   constexpr int Q = RS / 4;
   const uint64_t far = TRUNC == SMOE_TRUNC_GRADIENT ? far_entries<RS>(bb, srec, n) : 0;
-  for (int k = 0; k < n; ++k)
-    forward_entry<C, ORDER, TRUNC, ROWS>(px, r2, cut_scale, cut_offset, &srec[k * Q],
-                                   (far >> k & 1) != 0, D, N);
+  auto one = [&](int k) {
+    float r[RS], e[ROWS], m[ROWS][C];
+    load_record<RS>(r, &srec[k * Q]);
+    entry_terms<C, ORDER, TRUNC, ROWS>(px, r2, cut_scale, cut_offset, r, (far >> k & 1) != 0, e, m);
+    add_terms<C, ROWS>(e, m, D, N);
+  };
+  int k = 0;
+  if (ROWS == 1) {
+    // one strip to a wave: an entry is one chain of dependent operations and few waves share
+    // the SIMD, so AHEAD entries are formed side by side and then added in order
+    constexpr int AHEAD = 4;
+    for (; k + AHEAD <= n; k += AHEAD) {
+      if ((far >> k & ((1u << AHEAD) - 1)) != 0) {
+        for (int i = 0; i < AHEAD; ++i) one(k + i);
+        continue;
+      }
+      float r[AHEAD][RS], e[AHEAD][ROWS], m[AHEAD][ROWS][C];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) load_record<RS>(r[i], &srec[(k + i) * Q]);
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i)
+        entry_terms<C, ORDER, TRUNC, ROWS>(px, r2, cut_scale, cut_offset, r[i], false, e[i], m[i]);
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) add_terms<C, ROWS>(e[i], m[i], D, N);
+    }
+  }
+  for (; k < n; ++k) one(k);
 }
 
 // A copy of x that the compiler must keep in a vector register: loop-invariant operands of
-// the forward's per-row arithmetic are read from VGPRs rather than SGPRs (see forward_entry).
+// the forward's per-row arithmetic are read from VGPRs rather than SGPRs (see entry_terms).
 __device__ __forceinline__ float in_vgpr(float x) {
   asm volatile("" : "+v"(x));
   return x;
@@ -349,8 +387,8 @@ __device__ __forceinline__ void zero_sums(float (&D)[ROWS], float (&N)[ROWS][C])
 // Forward accumulation over a block's list [rg.x, rg.y) in list order (forward_chunk per
 // chunk, records staged through LDS in chunks).
 // shift: list entries hold the kernel id << shift.  ent: null, or LDS room for one chunk of
-// entries, which the staging then reads from there (a single-chunk list already holds them,
-// sorted; longer lists copy each chunk's entries in).
+// entries for the staging to go by.  staged: the list is one chunk and its records stand in
+// srec already.
 template <int C, int ORDER, int TRUNC, int WAVES>
 __device__ __forceinline__ void forward_accumulate(const PixelCoords<kStrips / WAVES>& px, const BlockBox& bb,
                                                    float r2, float cut_scale, float cut_offset,
@@ -358,7 +396,8 @@ __device__ __forceinline__ void forward_accumulate(const PixelCoords<kStrips / W
                                                    const uint32_t* __restrict__ vals, int shift,
                                                    int2 rg, float4* srec, float (&D)[kStrips / WAVES],
                                                    float (&N)[kStrips / WAVES][C],
-                                                   uint32_t* ent = nullptr) {
+                                                   uint32_t* ent = nullptr,
+                                                   bool staged = false) {
   constexpr int RS = record_stride(C, ORDER);
   zero_sums<C>(D, N);
   if (TRUNC == SMOE_TRUNC_RENDER) {
@@ -367,7 +406,9 @@ __device__ __forceinline__ void forward_accumulate(const PixelCoords<kStrips / W
   }
   for (int base = rg.x; base < rg.y; base += kChunk) {
     const int n = __builtin_amdgcn_readfirstlane(min(kChunk, rg.y - base));
-    if (ent) stage_records_lds<RS, WAVES>(srec, records, vals, base, n, shift, ent, rg.y - rg.x <= kChunk);
+    if (staged) {
+      // (nothing to load)
+    } else if (ent) stage_records_lds<RS, WAVES>(srec, records, vals, base, n, shift, ent);
     else stage_records<RS, WAVES>(srec, records, vals, base, n, shift);
     forward_chunk<C, ORDER, TRUNC, kStrips / WAVES>(px, bb, r2, cut_scale, cut_offset, srec, n, D, N);
   }
@@ -657,9 +698,58 @@ __device__ __forceinline__ EllipseBox ellipse_box(const BlockBox& bb, float r, f
 
 // Scratch of the backward in LDS, beside the pixel seeds.
 struct BackwardScratch {
-  uint32_t ent[kChunk];  // the chunk's list entries, then sort keys, then packed boxes
-  uint2 out[kChunk];     // (kernel id, partial row) in processing order
+  uint32_t ent[kChunk];  // the chunk's list entries, then packed boxes
+  uint2 out[kChunk];     // (kernel id or staged record, partial row) in processing order
 };
+
+// The partial row of a list entry (Backward, below) at position pos of the lists; list0: the
+// first position of its list.
+__device__ __forceinline__ uint32_t partial_row(uint32_t e, int shift, bool packed, int pos, int K,
+                                                int list0) {
+  if (!packed) return (uint32_t)pos;
+  const uint32_t low = e & ((1u << shift) - 1u);
+  return low < (uint32_t)kSlots ? (e >> shift) * (uint32_t)kSlots + low
+                                : (uint32_t)K * kSlots + (uint32_t)list0 + (low - kSlots);
+}
+
+// One wave lays out the backward of a chunk of n <= 64 entries, a lane per entry (lanes from n
+// on pass anything): f, i22 = its record's first fields, at = where its record is, row = its
+// partial row.  Leaves in sc, in processing order, the box of pixels its ellipse reaches as
+// first row | first column << 4 | log2 rows per step << 8 | pairs of steps << 12, and (at, row).
+__device__ __forceinline__ void lay_out_entries(const BlockBox& bb, float radius, int n, float4 f,
+                                                float i22, uint32_t at, uint32_t row,
+                                                BackwardScratch& sc) {
+  const int lane = threadIdx.x & 63;
+  int its = 0, packed_box = 0;
+  if (lane < n) {
+    const EllipseBox b = ellipse_box(bb, radius, f.x, f.y, f.z, f.w, i22);
+    if (b.row0 <= b.row1) {
+      const int lw = max(1, 32 - __clz(b.col1 - b.col0));  // columns <= 2^lw
+      const int lr = 4 - lw;                               // 2^lr rows per step
+      its = (b.row1 - b.row0 + (2 << lr)) >> (lr + 1);
+      // (the last steps' rows and columns stay inside the block)
+      packed_box = min(b.row0, 16 - (its << (lr + 1))) | min(b.col0, 16 - (1 << lw)) << 4 |
+                   lr << 8 | its << 12;
+    }
+  }
+  // place by step count (8 .. 0), most first, ties in the lanes' order
+  int to = 0, before = 0;
+#pragma unroll
+  for (int v = 8; v >= 0; --v) {
+    const uint64_t same = __ballot(lane < n && its == v);
+    const int place = (int)__builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, (uint32_t)before));
+    to = its == v ? place : to;
+    before += __popcll(same);
+  }
+  const uint32_t first = __builtin_amdgcn_readfirstlane(at);
+  if (lane >= n) {  // padding, after every entry: its lanes work on the first one's record
+    to = lane;
+    at = first;
+  }
+  sc.ent[to] = (uint32_t)packed_box;
+  sc.out[to] = make_uint2(at, row);
+}
 
 // Backward over a block's list [rg.x, rg.y): for every kernel the adjoints of its 6 + 3C raw
 // parameters, summed over the block's 256 pixels (pi K recomputed from the record, w = pi K /
@@ -685,8 +775,8 @@ struct BackwardScratch {
 // several waves to a block, they take the groups in turn.
 // Measured against one entry per wave: the 2048^2 RGB linear fit step 145 -> 117 us (65536
 // kernels, 26-entry lists), the standalone backward of a 509x381 render 20.3 -> 13.7 us.
-// The seeds sit in LDS, where the forward's records were; a lane reads its entry's record
-// from memory.
+// The seeds sit in LDS; a lane reads its entry's record from memory, or, where the forward's
+// records still stand beside the seeds (staged, lists of one chunk), from there.
 //
 // Per lane, over its pixels: the sums that do not factor through the column -- A_c =
 // sum g_c w, Y_c = sum g_c w dy, V = sum H (dy - t), S2 = sum H z2^2, R = sum H.  dx and z1 are
@@ -698,7 +788,8 @@ struct BackwardScratch {
 // rectangle: kernel-major rows), else row kSlots K + rg.x + low - kSlots (its bucket slot),
 // where the fit step's gather reads it; otherwise the entry's list position.
 // x0, y0: o + 0.5 + (column, row) of the block's first pixel, whose coordinates are these
-// times inv_s; UNIT: inv_s = 1.  ent_ready: sc.ent holds a single-chunk list already.
+// times inv_s; UNIT: inv_s = 1.  laid_out: the list is one chunk and sc holds its layout
+// (lay_out_entries); staged: null, or where its records stand in LDS, by the layout's places.
 template <int C, int ORDER, bool UNIT, int WAVES>
 __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0, float y0,
                                                     float inv_s, float radius, float r2,
@@ -706,7 +797,7 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
                                                     const uint32_t* __restrict__ vals, int shift,
                                                     bool packed, int2 rg,
                                                     const PixelSeed<C>* seeds, BackwardScratch& sc,
-                                                    bool ent_ready,
+                                                    bool laid_out, const float4* staged,
                                                     float* __restrict__ pair_grads, int K = 0) {
   constexpr int RS = record_stride(C, ORDER);
   constexpr int Q = RS / 4;
@@ -715,52 +806,24 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
   static_assert(PS <= 16, "16 accumulators per kernel");
   const int lane = threadIdx.x & 63;
   const int l16 = lane & 15, sub = lane >> 4, wave = wave_index<WAVES>();
-  const uint32_t slot_mask = (1u << shift) - 1u;
   for (int base = rg.x; base < rg.y; base += kChunk) {
     const int n = __builtin_amdgcn_readfirstlane(min(kChunk, rg.y - base));
     __syncthreads();
-    if (wave == 0) {
-      // a lane per entry: its partial row, its box, its pairs of steps
-      uint32_t e = 0, row = 0;
-      int its = 0, packed_box = 0;
-      if (lane < n) {
-        e = ent_ready && rg.y - rg.x <= kChunk ? sc.ent[lane] : vals[base + lane];
-        const uint32_t low = e & slot_mask;
-        row = !packed ? (uint32_t)(base + lane)
-                      : (low < (uint32_t)kSlots ? (e >> shift) * (uint32_t)kSlots + low
-                                                : (uint32_t)K * kSlots + (uint32_t)rg.x + (low - kSlots));
+    if (!laid_out) {
+      if (wave == 0) {
+        const uint32_t e = lane < n ? vals[base + lane] : 0u;
         const float4* r4 = reinterpret_cast<const float4*>(records + (size_t)(e >> shift) * RS);
-        const float4 f = r4[0];
-        const EllipseBox b = ellipse_box(bb, radius, f.x, f.y, f.z, f.w, r4[1].x);
-        if (b.row0 <= b.row1) {
-          const int lw = max(1, 32 - __clz(b.col1 - b.col0));  // columns <= 2^lw
-          const int lr = 4 - lw;                               // 2^lr rows per step
-          its = (b.row1 - b.row0 + (2 << lr)) >> (lr + 1);
-          // (the last steps' rows and columns stay inside the block)
-          packed_box = min(b.row0, 16 - (its << (lr + 1))) | min(b.col0, 16 - (1 << lw)) << 4 |
-                       lr << 8 | its << 12;
+        float4 f = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float i22 = 0.0f;
+        if (lane < n) {
+          f = r4[0];
+          i22 = r4[1].x;
         }
+        lay_out_entries(bb, radius, n, f, i22, e >> shift,
+                        partial_row(e, shift, packed, base + lane, K, rg.x), sc);
       }
-      const uint32_t id = lane < n ? e >> shift : __builtin_amdgcn_readfirstlane(e >> shift);
-      wave_sync();
-      // rank by step count, most first, ties in list order
-      const uint32_t key = (uint32_t)its << 6 | (uint32_t)(63 - lane);
-      sc.ent[lane] = key;
-      wave_sync();
-      int at = 0;
-      {
-        const uint4* k4 = reinterpret_cast<const uint4*>(sc.ent);
-        for (int j = 0; j < (n + 3) >> 2; ++j) {
-          const uint4 q = k4[j];
-          at += (q.x > key ? 1 : 0) + (q.y > key ? 1 : 0) + (q.z > key ? 1 : 0) + (q.w > key ? 1 : 0);
-        }
-      }
-      if (lane >= n) at = lane;  // (padding: keys below every entry's)
-      wave_sync();
-      sc.ent[at] = (uint32_t)packed_box;
-      sc.out[at] = make_uint2(id, row);
+      __syncthreads();
     }
-    __syncthreads();
     for (int g = 4 * wave; g < n; g += 4 * WAVES) {
       const uint32_t bx = sc.ent[g + sub];
       const uint2 out = sc.out[g + sub];
@@ -768,17 +831,8 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
       float tot = 0.0f;
       if (M > 0) {
         float r[RS];
-        {
-          const float4* r4 = reinterpret_cast<const float4*>(records + (size_t)out.x * RS);
-#pragma unroll
-          for (int q = 0; q < Q; ++q) {
-            const float4 f = r4[q];
-            r[4 * q] = f.x;
-            r[4 * q + 1] = f.y;
-            r[4 * q + 2] = f.z;
-            r[4 * q + 3] = f.w;
-          }
-        }
+        load_record<RS>(r, staged ? staged + out.x * Q
+                                  : reinterpret_cast<const float4*>(records + (size_t)out.x * RS));
         const int lr = (int)(bx >> 8 & 7u), mine = (int)(bx >> 12);
         const int col = (int)(bx >> 4 & 15u) + (l16 & ((16 >> lr) - 1));
         const int row0 = (int)(bx & 15u) + (l16 >> (4 - lr));

@@ -9,6 +9,8 @@
 // is also the block ranges), a scatter into the buckets, and a per-bucket ranking of the
 // kernel ids that restores the stable order the atomic scatter does not keep.
 // Every pass is integer work over a few MB, so the design minimises launches, not bytes.
+// A small single raster has the same arrays from its blocks' side instead, in one or two launches
+// (k_block_lists).
 // The fit step uses fixed-width buckets instead (k_scatter_fixed): no histogram and no scan,
 // the bucket of block t is entries [t W, t W + W) of the pair storage.
 #include <type_traits>
@@ -48,12 +50,57 @@ __device__ __forceinline__ int binning_kernel(int g, int K) {
   return (g | 127) < K ? (g & ~127) + ((g & 15) << 3) + ((g >> 4) & 7) : g;
 }
 
+// A kernel row's factor as its raster sees it (native sharpening: L / f, a correctly rounded
+// binary32 division), whether every parameter is finite, and the blocks it covers (none if not:
+// such a row takes part nowhere).
+// The np parameters are loaded together: a loop that stops at the first bad one waits for each
+// (k_block_lists at 16 blocks 8.1 -> 7.0 us, the render of 65536 kernels at 2048^2 79 -> 76.5).
+constexpr int kRowMax = num_params(3, 1);
+struct RowBoxes {
+  float l11, l21, l22;
+  bool finite;
+  KernelRects rects;
+};
+__device__ __forceinline__ RowBoxes row_boxes(const float* __restrict__ p, int np,
+                                              const SegGrid& sg, const Segs& S) {
+  float v[kRowMax];
+#pragma unroll
+  for (int k = 0; k < kRowMax; ++k) v[k] = p[min(k, np - 1)];
+  RowBoxes r;
+  r.l11 = v[2];
+  r.l21 = v[3];
+  r.l22 = v[4];
+  if (sg.sharpen != 1.0f) {
+    r.l11 = r.l11 / sg.sharpen;
+    r.l21 = r.l21 / sg.sharpen;
+    r.l22 = r.l22 / sg.sharpen;
+  }
+  int bad = (__builtin_isfinite(r.l11) ? 0 : 1) | (__builtin_isfinite(r.l21) ? 0 : 1) |
+            (__builtin_isfinite(r.l22) ? 0 : 1);
+#pragma unroll
+  for (int k = 0; k < kRowMax; ++k) bad |= __builtin_isfinite(v[k]) ? 0 : 1;
+  r.finite = bad == 0;
+  if (r.finite) {
+    r.rects = kernel_rects(v[0], v[1], r.l11, r.l21, r.l22, sg, S.r, S.box, S.trunc);
+  } else {
+    r.rects.tile = r.rects.native = make_int4(0, 0, -1, -1);
+  }
+  return r;
+}
+
+// Where a non-finite row is reported: at once, in the status word (COUNT and BOXES), or, where
+// no launch before this one has cleared the word, by the row's rectangle in tile_rects
+// (MARK: kMarkedRow in .w; as empty as any, and k_block_lists replaces it).  MARK also clears
+// the longest list, which k_block_lists raises.
+constexpr int kMarkedRow = -2;
+enum class Rows { COUNT, BOXES, MARK };
+
 // Every lane of a kernel's group reads the row and computes the output-block and native-block
 // rectangles; lane 0 writes them and the count, lane q the q-th float4 of the render record,
-// and (tile_counts not null) lane q adds one to the counts of the kernel's covered blocks q, q +
+// and (COUNT) lane q adds one to the counts of the kernel's covered blocks q, q +
 // LANES, ... (row-major).  A row with a NaN or infinite parameter covers no block (it takes
 // part nowhere) and sets the non-finite status word.
-template <int LANES>
+template <int LANES, Rows ROWS>
 __global__ __launch_bounds__(256) void k_preprocess(int C, int order,
                                                     const float* __restrict__ params, Segs S,
                                                     int4* __restrict__ tile_rects,
@@ -64,35 +111,23 @@ __global__ __launch_bounds__(256) void k_preprocess(int C, int order,
                                                     int32_t* __restrict__ status) {
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   const int g = gid / LANES, lq = gid % LANES;
+  if (ROWS == Rows::MARK && gid == 0) status[2] = 0;
   if (g >= S.K) return;
   const int j = binning_kernel(g, S.K);
   const SegGrid sg = seg_of_kernel(S, j);
   const int ne = expert_floats(C, order);
   const float* p = params + (size_t)(sg.param_offset + (j - sg.kernel_offset)) * (6 + ne);
-  // native sharpening: the raster sees L / f (a correctly rounded binary32 division)
-  float l11 = p[2], l21 = p[3], l22 = p[4];
-  if (sg.sharpen != 1.0f) {
-    l11 = l11 / sg.sharpen;
-    l21 = l21 / sg.sharpen;
-    l22 = l22 / sg.sharpen;
-  }
-  bool finite = __builtin_isfinite(l11) && __builtin_isfinite(l21) && __builtin_isfinite(l22);
-  for (int k = 0; k < 6 + ne; ++k) finite = finite && __builtin_isfinite(p[k]);
-  KernelRects kr;
-  if (finite) {
-    kr = kernel_rects(p[0], p[1], l11, l21, l22, sg, S.r, S.box, S.trunc);
-  } else {
-    kr.tile = kr.native = make_int4(0, 0, -1, -1);
-  }
-  const int4 rc = kr.tile;
+  const RowBoxes row = row_boxes(p, 6 + ne, sg, S);
+  const int4 rc = row.rects.tile;
   if (lq == 0) {
-    tile_rects[j] = rc;
-    native_rects[j] = kr.native;
+    tile_rects[j] = ROWS == Rows::MARK && !row.finite ? make_int4(0, 0, -1, kMarkedRow) : rc;
+    native_rects[j] = row.rects.native;
     counts[j] = rect_count(rc);
-    if (!finite) status[kNonfinite] = 1;
+    if (ROWS != Rows::MARK && !row.finite) status[kNonfinite] = 1;
   }
-  if (lq < rs / 4) write_record_quad(records + (size_t)j * rs, p, ne, lq, l11, l21, l22);
-  if (tile_counts) count_blocks(rc, sg, tile_counts, lq, LANES);
+  if (lq < rs / 4)
+    write_record_quad(records + (size_t)j * rs, p, ne, lq, row.l11, row.l21, row.l22);
+  if (ROWS == Rows::COUNT) count_blocks(rc, sg, tile_counts, lq, LANES);
 }
 
 // Exclusive scan of the per-block counts into [begin, end) ranges, with P, the overflow flag
@@ -342,6 +377,206 @@ __global__ __launch_bounds__(64 * kSortBlocks) void k_sort_buckets(int T,
   }
 }
 
+// The whole ordering of a small raster in one kernel, by its blocks instead of its pairs: a
+// block's list is read off the kernels' rectangles.  A lane holds a rectangle, and whether each
+// of 64 kernels covers a block is one ballot, whose set bits are already in the order of the
+// ids: no histogram, no atomics on counters, no sort.  Where a workgroup's lists begin it works
+// out by itself, from the number of each rectangle's blocks that lie before its own.  The work
+// grows with kernels times blocks (kListPairs), but a chunk of 64 kernels that misses the
+// workgroup's blocks altogether -- neighbouring ids are neighbours in the image -- costs one
+// test, and a kernel that covers every block costs what any other does, where the counters'
+// atomics queue up.  What bounds it is the latency of its phases (loads, ballots, two
+// scans, stores), so the rectangles of four chunks are loaded ahead (at 16384 kernels and 4096
+// blocks 30.0 -> 24.4 us); the figures against the other binning are with the rule below.
+//
+// ROWS_TOO: a single workgroup takes all blocks, and each lane works its kernel's row out itself
+// (k_preprocess's work: one launch less).  Otherwise k_preprocess<MARK> has run, and a
+// workgroup takes kListBlocks blocks, one for each of its waves.
+struct ListArgs {
+  Segs S;  // a single raster (no table)
+  int C, order;
+  const float* __restrict__ params;
+  int4* __restrict__ tile_rects;
+  int4* __restrict__ native_rects;
+  int32_t* __restrict__ counts;
+  float* __restrict__ records;
+  int rs;
+  int32_t* __restrict__ tile_counts;
+  int2* __restrict__ ranges;
+  uint32_t* __restrict__ keys;
+  uint32_t* __restrict__ vals;
+  int capacity;
+  int32_t* __restrict__ status;
+};
+constexpr int kListWaves = 8, kListThreads = 64 * kListWaves, kListBlocks = kListWaves;
+constexpr int kListMasks = 2048;  // ballots a workgroup keeps (blocks x chunks of 64 kernels)
+
+template <bool ROWS_TOO>
+__global__ __launch_bounds__(kListThreads) void k_block_lists(ListArgs a) {
+  __shared__ uint64_t s_mask[kListMasks];  // [block][chunk]
+  __shared__ int s_list[kListThreads];     // a block's entries, then where they begin
+  __shared__ int s_before[kListWaves], s_total[kListWaves], s_odd[kListWaves];
+  __shared__ int s_scan[kListWaves], s_longest[kListWaves];
+  const SegGrid sg = seg_grid_of(a.S.one);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int K = a.S.K, chunks = (K + 63) >> 6;
+  const int t0 = ROWS_TOO ? 0 : blockIdx.x * kListBlocks;
+  const int nb = ROWS_TOO ? a.S.T : min(kListBlocks, a.S.T - t0);
+  // the workgroup's blocks: from (tx0, ty0) on in row-major order; inside [xa, xb] x [ty0, ty1]
+  const int tx0 = t0 % sg.ntx, ty0 = t0 / sg.ntx, ty1 = (t0 + nb - 1) / sg.ntx;
+  const int xa = ty0 == ty1 ? tx0 : 0, xb = ty0 == ty1 ? (t0 + nb - 1) % sg.ntx : sg.ntx - 1;
+
+  int before = 0, total = 0, odd = 0;  // (at most kListPairs)
+  // one chunk's rectangles against the blocks
+  auto chunk = [&](int c, int4 rc) {
+    const int n = rect_count(rc), w = rc.z - rc.x + 1;
+    total += n;
+    if (n > 0) {
+      before += w * min(max(ty0 - rc.y, 0), rc.w - rc.y + 1);
+      if (rc.y <= ty0 && ty0 <= rc.w) before += min(max(tx0 - rc.x, 0), w);
+    }
+    if (__ballot(n > 0 && rc.y <= ty1 && rc.w >= ty0 && rc.x <= xb && rc.z >= xa) != 0) {
+      int tx = tx0, ty = ty0;
+      for (int b = 0; b < nb; ++b) {
+        const uint64_t m = __ballot(rc.x <= tx && tx <= rc.z && rc.y <= ty && ty <= rc.w);
+        if (lane == 0) s_mask[b * chunks + c] = m;
+        if (++tx == sg.ntx) {
+          tx = 0;
+          ++ty;
+        }
+      }
+    } else {
+      for (int b = lane; b < nb; b += 64) s_mask[b * chunks + c] = 0;
+    }
+  };
+  const int4 none = make_int4(0, 0, -1, -1);
+  if (ROWS_TOO) {
+    for (int c = wave; c < chunks; c += kListWaves) {
+      const int j = 64 * c + lane;
+      int4 rc = none;
+      if (j < K) {
+        const int ne = expert_floats(a.C, a.order);
+        const float* p = a.params + (size_t)(sg.param_offset + j) * (6 + ne);
+        const RowBoxes row = row_boxes(p, 6 + ne, sg, a.S);
+        rc = row.rects.tile;
+        odd |= row.finite ? 0 : 1;
+        a.tile_rects[j] = rc;
+        a.native_rects[j] = row.rects.native;
+        a.counts[j] = rect_count(rc);
+        for (int q = 0; q < a.rs / 4; ++q)
+          write_record_quad(a.records + (size_t)j * a.rs, p, ne, q, row.l11, row.l21, row.l22);
+      }
+      chunk(c, rc);
+    }
+  } else {
+    constexpr int AHEAD = 4;  // chunks on their way
+    for (int c0 = wave; c0 < chunks; c0 += AHEAD * kListWaves) {
+      int4 rc[AHEAD];
+#pragma unroll
+      for (int k = 0; k < AHEAD; ++k) {
+        const int j = 64 * (c0 + k * kListWaves) + lane;
+        rc[k] = a.tile_rects[min(j, K - 1)];
+        if (j >= K) rc[k] = none;
+      }
+#pragma unroll
+      for (int k = 0; k < AHEAD; ++k) {
+        const int c = c0 + k * kListWaves;
+        if (c >= chunks) break;
+        if (rc[k].w == kMarkedRow) {
+          odd = 1;
+          if (blockIdx.x == 0) a.tile_rects[64 * c + lane] = none;
+        }
+        chunk(c, rc[k]);
+      }
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    before += __shfl_xor(before, off);
+    total += __shfl_xor(total, off);
+    odd |= __shfl_xor(odd, off);
+  }
+  if (lane == 0) {
+    s_before[wave] = before;
+    s_total[wave] = total;
+    s_odd[wave] = odd;
+  }
+  __syncthreads();
+  before = total = odd = 0;
+  for (int v = 0; v < kListWaves; ++v) {
+    before += s_before[v];
+    total += s_total[v];
+    odd |= s_odd[v];
+  }
+  const bool over = total > a.capacity;
+
+  // the blocks' entries: a few chunks each, counted by a thread, or many, by a wave
+  if (ROWS_TOO) {
+    int n = 0;
+    if (tid < nb)
+      for (int c = 0; c < chunks; ++c) n += __popcll(s_mask[tid * chunks + c]);
+    s_list[tid] = n;
+  } else if (wave < nb) {
+    int n = 0;
+    for (int c = lane; c < chunks; c += 64) n += __popcll(s_mask[wave * chunks + c]);
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
+    if (lane == 0) s_list[wave] = n;
+  }
+  __syncthreads();
+  const int n = tid < nb ? s_list[tid] : 0;
+  int incl = n, longest = n;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(incl, off);
+    if (lane >= off) incl += o;
+    longest = max(longest, __shfl_xor(longest, off));
+  }
+  if (lane == 63) {
+    s_scan[wave] = incl;
+    s_longest[wave] = longest;
+  }
+  __syncthreads();
+  int begin = before + incl - n;
+  for (int v = 0; v < kListWaves; ++v) {
+    if (v < wave) begin += s_scan[v];
+    longest = max(longest, s_longest[v]);
+  }
+  if (tid < nb) {
+    s_list[tid] = begin;
+    a.ranges[t0 + tid] = over ? make_int2(0, 0) : make_int2(begin, begin + n);
+    a.tile_counts[t0 + tid] = 0;
+  }
+  if (tid == 0) {
+    if (ROWS_TOO) a.status[2] = longest;
+    else atomicMax(&a.status[2], longest);
+    if (blockIdx.x == 0) {
+      a.status[0] = total;
+      a.status[1] = over ? 1 : 0;
+      a.status[kNonfiniteOut] = a.status[kNonfinite] = odd;
+    }
+  }
+  if (over) return;  // (the same for all threads of all workgroups)
+  __syncthreads();
+  for (int b = wave; b < nb; b += kListWaves) {
+    int pos = __builtin_amdgcn_readfirstlane(s_list[b]);
+    for (int c0 = 0; c0 < chunks; c0 += 64) {
+      const uint64_t mine = c0 + lane < chunks ? s_mask[b * chunks + c0 + lane] : 0;
+      for (uint64_t left = __ballot(mine != 0); left != 0; left &= left - 1) {
+        const int c = __builtin_ctzll(left);
+        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)mine, c);
+        const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(mine >> 32), c);
+        const uint64_t m = (uint64_t)hi << 32 | lo;
+        if (m >> lane & 1) {
+          const int at = pos + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+          a.vals[at] = (uint32_t)(64 * (c0 + c) + lane);
+          a.keys[at] = (uint32_t)(t0 + b);
+        }
+        pos += __popcll(m);
+      }
+    }
+  }
+}
+
 // A fit's first kernel: zero the bucket cursors and the status words (P, overflow, longest list,
 // step shadow, the overflow flags and the non-finite flag), whatever the workspace held before.
 __global__ void k_prepare_fit(int32_t* __restrict__ cursors, int n, int32_t* __restrict__ status) {
@@ -364,15 +599,60 @@ __global__ void k_copy_i32(const int32_t* __restrict__ src, int32_t* __restrict_
 
 inline int cdiv(long long a, int b) { return (int)((a + b - 1) / b); }
 
+template <Rows ROWS>
 void preprocess(int C, int order, const float* params, const Segs& S, const smoe_bins& b,
-                int32_t* tile_counts, hipStream_t s) {
+                hipStream_t s) {
   with_lanes(S, [&](auto lanes) {
     constexpr int L = decltype(lanes)::value;
-    k_preprocess<L><<<cdiv((long long)S.K * L, 256), 256, 0, s>>>(
+    k_preprocess<L, ROWS><<<cdiv((long long)S.K * L, 256), 256, 0, s>>>(
         C, order, params, S, reinterpret_cast<int4*>(b.tile_rects),
-        reinterpret_cast<int4*>(b.native_rects), b.counts, b.records, b.record_stride, tile_counts,
-        b.status);
+        reinterpret_cast<int4*>(b.native_rects), b.counts, b.records, b.record_stride,
+        b.tile_counts, b.status);
   });
+}
+
+// Rasters whose lists k_block_lists makes.  Measured, the binning by counters and sorts against
+// this one: 64 kernels on 64^2 16.9 / 7.0 us, 1024 on 256^2 17.7 / 9.3, 4096 on 512^2 18.5 /
+// 11.7, 8192 on 724^2 (2^24 pairs) 20.9 / 15.8, 16384 on 1024^2 (2^26) 22.8 / 24.4; wide kernels
+// are never slower, 2048 on 256^2 with 241 000 entries 167 / 15, 4000 on 512^2 with 620 000 entries
+// 116 / 18.  Of 4, 8 and 16 blocks to a workgroup eight are the best at 512^2 (12.7 / 11.7 / 13.1
+// us); four are 0.4 us faster at 256^2 and 7.7 us slower at 1024^2.
+constexpr int kListKernels = kListMasks / kListBlocks * 64, kListTiles = 4096;
+constexpr long long kListPairs = 1ll << 25;
+inline bool lists_by_block(const Segs& S) {
+  return !S.tab && S.K > 0 && S.K <= kListKernels && S.T <= kListTiles &&
+         (long long)S.K * S.T <= kListPairs;
+}
+// ... and by a single workgroup, with their rows: 16 ballots (64^2) 7.0 us and one launch,
+// 64 about the time of the two launches, 256 14.5 us against 8.5.
+inline bool lists_at_once(const Segs& S) {
+  return S.K <= kListThreads && S.T <= kListThreads && cdiv(S.K, 64) * S.T <= 64;
+}
+
+hipError_t launch_block_lists(int C, int order, const float* params, const Segs& S,
+                              const smoe_bins& b, hipStream_t s) {
+  const ListArgs a{S,
+                   C,
+                   order,
+                   params,
+                   reinterpret_cast<int4*>(b.tile_rects),
+                   reinterpret_cast<int4*>(b.native_rects),
+                   b.counts,
+                   b.records,
+                   b.record_stride,
+                   b.tile_counts,
+                   reinterpret_cast<int2*>(b.ranges),
+                   b.keys,
+                   b.vals,
+                   b.capacity,
+                   b.status};
+  if (lists_at_once(S)) {
+    k_block_lists<true><<<1, kListThreads, 0, s>>>(a);
+  } else {
+    preprocess<Rows::MARK>(C, order, params, S, b, s);
+    k_block_lists<false><<<cdiv(S.T, kListBlocks), kListThreads, 0, s>>>(a);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -383,7 +663,7 @@ hipError_t launch_count(int C, int order, const float* params, const Segs& S,
   // node, so that the step can be captured into a graph).
   k_fill_counts<<<cdiv(S.T, 256), 256, 0, s>>>(b.tile_counts, S.T, b.status);
   if (S.K > 0) {
-    preprocess(C, order, params, S, b, b.tile_counts, s);
+    preprocess<Rows::COUNT>(C, order, params, S, b, s);
   }
   return hipGetLastError();
 }
@@ -405,7 +685,7 @@ hipError_t launch_prepare_fit(int C, int order, const float* params, const Segs&
                               const smoe_bins& b, hipStream_t s) {
   k_prepare_fit<<<cdiv(S.T, 256), 256, 0, s>>>(b.tile_counts, S.T, b.status);
   if (S.K > 0) {
-    preprocess(C, order, params, S, b, nullptr, s);
+    preprocess<Rows::BOXES>(C, order, params, S, b, s);
   }
   return hipGetLastError();
 }
@@ -438,6 +718,7 @@ hipError_t launch_copy_status(const smoe_bins& b, int32_t* out4, hipStream_t s) 
 
 hipError_t launch_bin(int C, int order, const float* params, const Segs& S, const smoe_bins& b,
                       hipStream_t s) {
+  if (lists_by_block(S)) return launch_block_lists(C, order, params, S, b, s);
   hipError_t e = launch_count(C, order, params, S, b, s);
   if (e == hipSuccess) e = launch_scan(S, b, s);
   if (e == hipSuccess) e = launch_scatter(S, b, s);

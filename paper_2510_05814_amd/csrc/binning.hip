@@ -592,11 +592,6 @@ __global__ void k_fill_counts(int32_t* __restrict__ counts, int n, int32_t* __re
   if (i == 0) status[kNonfinite] = 0;
 }
 
-__global__ void k_copy_i32(const int32_t* __restrict__ src, int32_t* __restrict__ dst, int n) {
-  const int i = threadIdx.x;
-  if (i < n) dst[i] = src[i];
-}
-
 inline int cdiv(long long a, int b) { return (int)((a + b - 1) / b); }
 
 template <Rows ROWS>
@@ -708,11 +703,6 @@ hipError_t launch_scatter(const Segs& S, const smoe_bins& b, hipStream_t s) {
         S, reinterpret_cast<const int4*>(b.tile_rects), reinterpret_cast<const int2*>(b.ranges),
         b.tile_counts, b.vals, b.status);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_copy_status(const smoe_bins& b, int32_t* out4, hipStream_t s) {
-  k_copy_i32<<<1, 64, 0, s>>>(b.status, out4, 4);
   return hipGetLastError();
 }
 

@@ -414,7 +414,8 @@ smoe_status smoe_render(const smoe_model* model, const smoe_grid* grid, const sm
   const bool loss = target && loss_out;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e =
-      launch_render(model->C, model->order, S, *bins, image, denom, loss ? target : nullptr, s);
+      launch_render(model->C, model->order, S, *bins, image, denom, loss ? target : nullptr,
+                    nullptr, s);
   if (e == hipSuccess && loss) {
     const float inv_n = (float)(1.0 / ((double)grid->width * grid->height * model->C));
     e = launch_loss_reduce(*bins, S.T, inv_n, loss_out, s);
@@ -457,7 +458,7 @@ smoe_status smoe_render_batched(const smoe_batch* batch, const smoe_bins* bins, 
   if (!batch_segs(batch, &S) || !bins_match(bins, S.K, batch->C, batch->order) || !images)
     return SMOE_ERR_INVALID;
   if (S.T > bins->max_tiles) return SMOE_ERR_TOO_LARGE;
-  return hip_status(launch_render(batch->C, batch->order, S, *bins, images, denoms, nullptr,
+  return hip_status(launch_render(batch->C, batch->order, S, *bins, images, denoms, nullptr, nullptr,
                                   static_cast<hipStream_t>(stream)));
 }
 
@@ -477,8 +478,8 @@ smoe_status smoe_render_noalloc(const smoe_model* model, const smoe_grid* grid, 
     return SMOE_ERR_TOO_LARGE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   e = launch_bin(model->C, model->order, model->params, S, b, s);
-  if (e == hipSuccess) e = launch_render(model->C, model->order, S, b, image, denom, nullptr, s);
-  if (e == hipSuccess && status_out) e = launch_copy_status(b, status_out, s);
+  if (e == hipSuccess)
+    e = launch_render(model->C, model->order, S, b, image, denom, nullptr, status_out, s);
   return hip_status(e);
 }
 

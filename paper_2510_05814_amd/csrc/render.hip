@@ -9,10 +9,10 @@
 // one v_exp_f32 per participating pair.
 //
 // Long lists (more than kSplitMin entries, which only very wide kernels produce) are split
-// over the four waves of a workgroup instead (k_render_wide): wave w accumulates the w-th
-// contiguous quarter of the list, and wave 0 adds the four partial sums in wave order -- a
-// fixed order, so the render stays deterministic.  Every block is rendered by exactly one of
-// the two kernels.
+// over the four waves of a workgroup instead: wave w accumulates the w-th contiguous quarter of
+// the list, and wave 0 adds the four partial sums in wave order -- a fixed order, so the render
+// stays deterministic.  On small rasters k_render has the four waves and does it itself; on
+// others k_render_wide does, and every block is rendered by exactly one of the two kernels.
 //
 // Optional fused squared error against a target: each block writes its sum of squared
 // errors to tile_loss[block]; launch_loss_reduce() then reduces those in a fixed order.
@@ -31,6 +31,7 @@ struct RenderArgs {
   const float* __restrict__ target;
   float* __restrict__ tile_loss;
   const int32_t* __restrict__ status;  // the binning's status words (word 2: longest list)
+  int32_t* __restrict__ status_out;    // null, or receives the first four
 };
 
 // Blocks whose list is longer than this go to k_render_wide.
@@ -80,40 +81,22 @@ __device__ __forceinline__ void render_epilogue(const RenderArgs& a, const SegGr
   }
 }
 
-template <int C, int ORDER, bool RBF, int TRUNC, int WAVES>
-__global__ __launch_bounds__(kWave * WAVES) void k_render(RenderArgs a) {
-  constexpr int ROWS = kStrips / WAVES;
-  __shared__ float s_err[WAVES == 1 ? 1 : kTilePixels];
-  __shared__ float4 srec[kChunk * record_stride(C, ORDER) / 4];
-  const int tile = xcd_block(blockIdx.x, a.S.T);
-  const int2 rg = a.ranges[tile];
-  if (rg.y - rg.x > kSplitMin) return;  // a long list: k_render_wide renders this block
-  const SegGrid sg = seg_of_tile(a.S, tile);
-  const PixelCoords<ROWS> px = lane_pixels<WAVES>(sg, tile - sg.tile_offset);
-  float D[ROWS], N[ROWS][C];
-  forward_accumulate<C, ORDER, TRUNC, WAVES>(px, block_box(sg, tile - sg.tile_offset), a.S.r2,
-                                             a.S.cut_scale, a.S.cut_offset, a.records, a.vals, 0,
-                                             rg, srec, D, N);
-  render_epilogue<C, RBF, WAVES>(a, sg, px, tile, D, N, s_err);
-}
-
-// Four waves per block for lists longer than kSplitMin.  Each wave stages its own records
-// in its own LDS region; within a wave, LDS stores and loads execute in program order, so
-// the staging needs no workgroup barrier (the waves' chunk counts differ).  A workgroup
-// walks the blocks with a grid stride (at most kWideGroups workgroups); a raster whose
-// longest list (status word 2 of its binning) is short costs only the launch.  Every
-// decision in the walk is the same for the four waves, so each barrier is reached by all
-// of them.
-constexpr int kWideGroups = 1024;
-
+// The four waves of a workgroup and one long list: each wave sums a contiguous quarter of it
+// and wave 0 adds the four.  Each wave stages its own records in its own LDS region; within a
+// wave, LDS stores and loads execute in program order, so the staging needs no workgroup
+// barrier (the waves' chunk counts differ).  The partial sums then take the records' place.
+template <int C, int ORDER>
+union WideScratch {
+  float4 srec[kSplitWaves][kChunk * record_stride(C, ORDER) / 4];
+  float part[kSplitWaves - 1][kStrips * (1 + C)][kWave];
+};
 template <int C, int ORDER, bool RBF, int TRUNC>
 __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile, int2 rg,
-                                                  float4 (*srec)[kChunk * record_stride(C, ORDER) / 4],
-                                                  float (*part)[kStrips * (1 + C)][kWave]) {
+                                                  WideScratch<C, ORDER>& sc) {
   constexpr int RS = record_stride(C, ORDER);
   constexpr int Q = RS / 4;
   const int len = rg.y - rg.x;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const SegGrid sg = seg_of_tile(a.S, tile);
   const PixelCoords<kStrips> px = lane_pixels<1>(sg, tile - sg.tile_offset);
   const int per = (len + kSplitWaves - 1) / kSplitWaves;
@@ -121,7 +104,7 @@ __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile,
   float D[kStrips], N[kStrips][C];
   zero_sums<C>(D, N);
   const float cut_scale = in_vgpr(a.S.cut_scale), cut_offset = in_vgpr(a.S.cut_offset);
-  float4* my = srec[wv];
+  float4* my = sc.srec[wv];
   const BlockBox bb = block_box(sg, tile - sg.tile_offset);
   for (int base = b; base < e; base += kChunk) {
     const int n = __builtin_amdgcn_readfirstlane(min(kChunk, e - base));
@@ -135,12 +118,13 @@ __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile,
     __builtin_amdgcn_wave_barrier();
     forward_chunk<C, ORDER, TRUNC, kStrips>(px, bb, a.S.r2, cut_scale, cut_offset, my, n, D, N);
   }
+  __syncthreads();  // every wave is done with its records
   if (wv > 0) {
 #pragma unroll
     for (int i = 0; i < kStrips; ++i) {
-      part[wv - 1][i * (1 + C)][lane] = D[i];
+      sc.part[wv - 1][i * (1 + C)][lane] = D[i];
 #pragma unroll
-      for (int c = 0; c < C; ++c) part[wv - 1][i * (1 + C) + 1 + c][lane] = N[i][c];
+      for (int c = 0; c < C; ++c) sc.part[wv - 1][i * (1 + C) + 1 + c][lane] = N[i][c];
     }
   }
   __syncthreads();
@@ -149,26 +133,63 @@ __device__ __forceinline__ void render_wide_block(const RenderArgs& a, int tile,
     for (int w = 0; w < kSplitWaves - 1; ++w) {
 #pragma unroll
       for (int i = 0; i < kStrips; ++i) {
-        D[i] += part[w][i * (1 + C)][lane];
+        D[i] += sc.part[w][i * (1 + C)][lane];
 #pragma unroll
-        for (int c = 0; c < C; ++c) N[i][c] += part[w][i * (1 + C) + 1 + c][lane];
+        for (int c = 0; c < C; ++c) N[i][c] += sc.part[w][i * (1 + C) + 1 + c][lane];
       }
     }
     render_epilogue<C, RBF, 1>(a, sg, px, tile, D, N, nullptr);
   }
-  __syncthreads();  // part is reused by the next block of the walk
 }
+
+// Four waves take their block's list whatever its length (a launch less: 64^2 grey 19.0 -> 12.0 us
+// together with the status words' copy), and blocks in the order of their ids: these rasters'
+// records fit every XCD's L2, while a band of blocks to an XCD gives the XCDs unequal
+// lists (4000 wide kernels on 512^2: 82.7 us against 74.4; lists of equal length the same).
+template <int C, int ORDER, bool RBF, int TRUNC, int WAVES>
+__global__ __launch_bounds__(kWave * WAVES) void k_render(RenderArgs a) {
+  constexpr int ROWS = kStrips / WAVES;
+  constexpr bool WIDE = WAVES == kSplitWaves;  // takes the long lists too
+  constexpr size_t kRecords = sizeof(float4) * kChunk * record_stride(C, ORDER) / 4;
+  __shared__ float s_err[WAVES == 1 ? 1 : kTilePixels];
+  __shared__ __align__(16) unsigned char
+      scratch[WIDE ? sizeof(WideScratch<C, ORDER>) : kRecords];
+  if (a.status_out && blockIdx.x == 0 && threadIdx.x < 4)
+    a.status_out[threadIdx.x] = a.status[threadIdx.x];
+  const int tile = WAVES > 1 ? (int)blockIdx.x : xcd_block(blockIdx.x, a.S.T);
+  const int2 rg = a.ranges[tile];
+  if (rg.y - rg.x > kSplitMin) {
+    if constexpr (WIDE)
+      render_wide_block<C, ORDER, RBF, TRUNC>(a, tile, rg,
+                                              *reinterpret_cast<WideScratch<C, ORDER>*>(scratch));
+    return;  // (else k_render_wide renders this block)
+  }
+  const SegGrid sg = seg_of_tile(a.S, tile);
+  const PixelCoords<ROWS> px = lane_pixels<WAVES>(sg, tile - sg.tile_offset);
+  float D[ROWS], N[ROWS][C];
+  forward_accumulate<C, ORDER, TRUNC, WAVES>(px, block_box(sg, tile - sg.tile_offset), a.S.r2,
+                                             a.S.cut_scale, a.S.cut_offset, a.records, a.vals, 0,
+                                             rg, reinterpret_cast<float4*>(scratch), D, N);
+  render_epilogue<C, RBF, WAVES>(a, sg, px, tile, D, N, s_err);
+}
+
+// The long lists of a raster whose k_render has one wave per block.  A workgroup
+// walks the blocks with a grid stride (at most kWideGroups workgroups); a raster whose
+// longest list (status word 2 of its binning) is short costs only the launch.  Every
+// decision in the walk is the same for the four waves, so each barrier is reached by all
+// of them.
+constexpr int kWideGroups = 1024;
 
 template <int C, int ORDER, bool RBF, int TRUNC>
 __global__ __launch_bounds__(kSplitWaves * kWave) void k_render_wide(RenderArgs a) {
-  __shared__ float4 srec[kSplitWaves][kChunk * record_stride(C, ORDER) / 4];
-  __shared__ float part[kSplitWaves - 1][kStrips * (1 + C)][kWave];
+  __shared__ WideScratch<C, ORDER> sc;
   // the binning recorded the longest list: without a long one there is nothing to walk
   if (a.status[2] <= kSplitMin) return;
   for (int tile = blockIdx.x; tile < a.S.T; tile += gridDim.x) {
     const int2 rg = a.ranges[tile];
     if (rg.y - rg.x <= kSplitMin) continue;  // k_render renders this block
-    render_wide_block<C, ORDER, RBF, TRUNC>(a, tile, rg, srec, part);
+    render_wide_block<C, ORDER, RBF, TRUNC>(a, tile, rg, sc);
+    __syncthreads();  // the scratch is reused by the next block of the walk
   }
 }
 
@@ -245,7 +266,8 @@ __global__ void k_zero_u64(unsigned long long* p, int n) {
 }  // namespace
 
 hipError_t launch_render(int C, int order, const Segs& S, const smoe_bins& b, float* image,
-                         float* denom, const float* target, hipStream_t s) {
+                         float* denom, const float* target, int32_t* status_out,
+                         hipStream_t s) {
   RenderArgs a{S,
                b.records,
                reinterpret_cast<const int2*>(b.ranges),
@@ -254,13 +276,16 @@ hipError_t launch_render(int C, int order, const Segs& S, const smoe_bins& b, fl
                denom,
                target,
                target ? b.tile_loss : nullptr,
-               b.status};
+               b.status,
+               status_out};
   with_shape(C, order, S, [&](auto sh) {
     using T = decltype(sh);
-    if (split_blocks(S))
-      k_render<T::C, T::ORDER, T::RBF, T::TRUNC, 4><<<S.T, 4 * kWave, 0, s>>>(a);
-    else
-      k_render<T::C, T::ORDER, T::RBF, T::TRUNC, 1><<<S.T, kWave, 0, s>>>(a);
+    if (split_blocks(S)) {
+      k_render<T::C, T::ORDER, T::RBF, T::TRUNC, kSplitWaves>
+          <<<S.T, kSplitWaves * kWave, 0, s>>>(a);
+      return;
+    }
+    k_render<T::C, T::ORDER, T::RBF, T::TRUNC, 1><<<S.T, kWave, 0, s>>>(a);
     k_render_wide<T::C, T::ORDER, T::RBF, T::TRUNC>
         <<<min(S.T, kWideGroups), kSplitWaves * kWave, 0, s>>>(a);
   });

@@ -191,8 +191,11 @@ constexpr int kSlots = 16;
 // per-kernel workspace array through kernel_offset; images through pixel_offset.
 hipError_t launch_bin(int C, int order, const float* params, const Segs& S, const smoe_bins& b,
                       hipStream_t s);
+// status_out: null, or receives the first four status words (P needed, overflow, longest
+// list, non-finite).
 hipError_t launch_render(int C, int order, const Segs& S, const smoe_bins& b, float* image,
-                         float* denom, const float* target, hipStream_t s);
+                         float* denom, const float* target, int32_t* status_out,
+                         hipStream_t s);
 hipError_t launch_pair_stats(const Segs& S, const smoe_bins& b, uint64_t* out2, hipStream_t s);
 hipError_t launch_loss_reduce(const smoe_bins& b, int T, float inv_n, float* loss_out,
                               hipStream_t s);
@@ -209,8 +212,6 @@ hipError_t launch_count(int C, int order, const float* params, const Segs& S,
                         const smoe_bins& b, hipStream_t s);
 hipError_t launch_scan(const Segs& S, const smoe_bins& b, hipStream_t s);
 hipError_t launch_scatter(const Segs& S, const smoe_bins& b, hipStream_t s);
-// Copies the first four status words (P needed, overflow, longest list, spare) to out4.
-hipError_t launch_copy_status(const smoe_bins& b, int32_t* out4, hipStream_t s);
 // Fit step: boxes and records of the current model with zeroed bucket cursors and status
 // words (the first step); then every step the scatter into fixed-width buckets (over each
 // kernel's box, computed from its model row), the fused per-block sort + render + backward,

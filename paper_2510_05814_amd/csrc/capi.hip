@@ -89,15 +89,18 @@ bool single_segs(const smoe_model* m, const smoe_grid* g, Segs* out) {
   set_render_bound(S);
   S.T = (int)raster_tiles(g->width, g->height, g->origin_x, g->origin_y);
   S.K = m->K;
+  S.max_scale = g->scale;
   *out = S;
   return true;
 }
 
 // Checks a host segment table (rasters valid, offsets equal to their running sums, model
 // rows inside [0, rows)) and returns its totals.
-bool check_segments(const smoe_segment* h, int32_t n, int32_t rows, int* T, int* K) {
+bool check_segments(const smoe_segment* h, int32_t n, int32_t rows, int* T, int* K,
+                    int* max_scale) {
   if (!h || n < 1) return false;
   long long t = 0, k = 0, px = 0;
+  int scale = 1;
   for (int i = 0; i < n; ++i) {
     const smoe_segment& s = h[i];
     if (!valid_raster(s.width, s.height, s.scale, s.origin_x, s.origin_y) ||
@@ -109,10 +112,12 @@ bool check_segments(const smoe_segment* h, int32_t n, int32_t rows, int* T, int*
     k += s.num_kernels;
     t += raster_tiles(s.width, s.height, s.origin_x, s.origin_y);
     px += (long long)s.width * s.height;
+    scale = std::max(scale, (int)s.scale);
   }
   if (t >= (1LL << 31) || k * 16 >= (1LL << 31)) return false;
   *T = (int)t;
   *K = (int)k;
+  *max_scale = scale;
   return true;
 }
 
@@ -123,7 +128,8 @@ bool batch_segs(const smoe_batch* b, Segs* out) {
     return false;
   Segs S;
   std::memset(&S, 0, sizeof(S));
-  if (!check_segments(b->segments_host, b->num_segments, b->num_params_rows, &S.T, &S.K))
+  if (!check_segments(b->segments_host, b->num_segments, b->num_params_rows, &S.T, &S.K,
+                      &S.max_scale))
     return false;
   S.tab = b->segments;
   S.n = b->num_segments;
@@ -196,7 +202,8 @@ bool fit_segs(const smoe_fit_state* st, Segs* S) {
         !valid_box(st->grid.box) || !valid_mode(st->grid.mode) || !valid_trunc(st->grid.trunc))
       return false;
     std::memset(S, 0, sizeof(*S));
-    if (!check_segments(st->segments_host, st->num_segments, st->K, &S->T, &S->K)) return false;
+    if (!check_segments(st->segments_host, st->num_segments, st->K, &S->T, &S->K, &S->max_scale))
+      return false;
     for (int i = 0; i < st->num_segments; ++i) {
       const smoe_segment& s = st->segments_host[i];
       if (s.scale != 1 || s.origin_x != 0 || s.origin_y != 0 ||

@@ -115,15 +115,6 @@ __device__ __forceinline__ int rect_count(int4 rc) {
   return rc.z < rc.x ? 0 : (rc.z - rc.x + 1) * (rc.w - rc.y + 1);
 }
 
-// One increment per covered block (global block ids): the histogram of the block-id digit.
-__device__ __forceinline__ void count_blocks(int4 rc, const SegGrid& g,
-                                             int32_t* __restrict__ tile_counts, int first = 0,
-                                             int stride = 1) {
-  const int n = rect_count(rc), w = rc.z - rc.x + 1;
-  for (int q = first; q < n; q += stride)
-    atomicAdd(&tile_counts[g.tile_offset + (rc.y + q / w) * g.ntx + rc.x + q % w], 1);
-}
-
 // Float4 number `quad` of the render record of a kernel row from its materialized parameter
 // row p (layout in smoe_internal.h; the record is 16-byte aligned): field f holds, beyond the
 // seven geometry fields, expert float f - 7 = p[f - 1], and zero padding after the experts.

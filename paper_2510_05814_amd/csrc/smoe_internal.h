@@ -57,6 +57,7 @@ struct Segs {
   int trunc;                             // SMOE_TRUNC_RENDER or SMOE_TRUNC_GRADIENT
   int T;                                 // blocks of all segments
   int K;                                 // kernel rows of all segments
+  int max_scale;                         // the largest scale of a segment
 };
 
 // A batch of rasters of a few blocks each (the windows of the multi-model estimator): a kernel
@@ -135,6 +136,18 @@ __device__ __forceinline__ int find_segment(const smoe_segment* __restrict__ tab
     else hi = mid - 1;
   }
   return lo;
+}
+
+// The output blocks of one native block (16 scale output pixels a side, beginning on a block) have
+// equal lists.  Along one axis of a raster whose first block is grid block b0: the first of its
+// blocks that lies in native block b.
+__host__ __device__ inline int native_first(int b, int scale, int b0) {
+  const int t = b * scale - b0;
+  return t > 0 ? t : 0;
+}
+// The native block of grid block b.
+__host__ __device__ inline int native_of(int b, int scale) {
+  return b >= 0 ? b / scale : -((scale - 1 - b) / scale);
 }
 
 // Segment of global block t: the last segment whose tile_offset <= t.

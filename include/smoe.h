@@ -219,7 +219,7 @@ typedef struct smoe_bins {
   int32_t* ranges;         /* [max_tiles][2] [begin, end) of each block's list */
   uint32_t* keys;          /* [capacity] block id of each pair, ascending */
   uint32_t* vals;          /* [capacity] kernel id of each pair, ascending within a block */
-  uint32_t* vals_alt;      /* [capacity] scratch for very long block lists */
+  uint32_t* vals_alt;      /* [capacity] scratch: block lists before they are ordered */
   float* pair_grads;       /* [16 K + capacity][NP rounded up to a multiple of 4] per-(block,
                               kernel) gradient partials (the centre's two without their
                               expert-slope terms, which the gradient gather adds once per

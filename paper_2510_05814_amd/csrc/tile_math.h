@@ -49,10 +49,11 @@ constexpr int kStrips = kTilePixels / kWave;   // 16x4 strips of a block (4)
 // Waves per block: one, or four (a strip each) on rasters whose blocks alone leave SIMDs idle
 // (1024 of them).  Four waves pay the column's terms four times over, one per SIMD waits on
 // its own latencies.  Measured, one wave against four, at 1024 / 1600 / 2025 / 2500 blocks:
-// RGB linear fit step 30.1 / 31.9 / 32.9 / 36.5 us against 26.8 / 30.8 / 33.3 / 37.7, render
-// 14.3 / 14.2 / 14.1 / 14.6 against 14.2 / 14.3 / 15.7 / 18.3.  The backward alone has no such
-// terms (its groups of entries are dealt out whole): 16.0 us against 13.8 at 1024 blocks, 24.1
-// against 24.0 at 3600, 30.1 against 28.7 at 5184, 37.1 against 37.9 at 7744.
+// RGB linear fit step 27.7 / 30.8 / 31.5 / 36.1 us against 24.7 / 32.1 / 34.6 / 39.3 (at 16 blocks
+// 23.8 against 18.2), render 14.3 / 13.9 / 13.9 / 14.6 against 13.9 / 15.1 / 17.4 / 19.4.  The
+// backward alone has no such terms (its groups of entries are dealt out whole): 15.9 us against
+// 12.8 at 1024 blocks, 23.6 against 23.4 at 3600, 30.2 against 28.8 at 5184, 37.1 against 37.9 at
+// 7744.
 // Lists of a few entries (few_blocks) give four waves nothing to share: one (a fit of 1392
 // windows of a block each 22.6 us against 23.5).
 constexpr int kSplitForward = 1536, kSplitBackward = 6144;
@@ -347,7 +348,8 @@ __device__ __forceinline__ void forward_chunk(const PixelCoords<ROWS>& px, const
   int k = 0;
   if (ROWS == 1) {
     // one strip to a wave: an entry is one chain of dependent operations and few waves share
-    // the SIMD, so AHEAD entries are formed side by side and then added in order
+    // the SIMD, so AHEAD entries are formed side by side and then added in order (with the
+    // records' loading during the ranking, four steps of a 64^2 grey fit 88.3 -> 77.9 us)
     constexpr int AHEAD = 4;
     for (; k + AHEAD <= n; k += AHEAD) {
       if ((far >> k & ((1u << AHEAD) - 1)) != 0) {

@@ -95,9 +95,11 @@ bool single_segs(const smoe_model* m, const smoe_grid* g, Segs* out) {
 }
 
 // Checks a host segment table (rasters valid, offsets equal to their running sums, model
-// rows inside [0, rows)) and returns its totals.
-bool check_segments(const smoe_segment* h, int32_t n, int32_t rows, int* T, int* K,
-                    int* max_scale) {
+// rows inside [0, rows)) and returns its totals and its largest scale.  FIT: the table of a fit
+// (native rasters, each with its own rows, unsharpened; the scale is then 1).  One walk: a fit step
+// over 17161 windows is issued about as fast as the table is checked.
+template <bool FIT>
+bool check_segments(const smoe_segment* h, int32_t n, int32_t rows, Segs* S) {
   if (!h || n < 1) return false;
   long long t = 0, k = 0, px = 0;
   int scale = 1;
@@ -106,18 +108,21 @@ bool check_segments(const smoe_segment* h, int32_t n, int32_t rows, int* T, int*
     if (!valid_raster(s.width, s.height, s.scale, s.origin_x, s.origin_y) ||
         !valid_sharpen(s.sharpen))
       return false;
+    if (FIT && (s.scale != 1 || s.origin_x != 0 || s.origin_y != 0 ||
+                s.param_offset != s.kernel_offset || !no_sharpen(s.sharpen)))
+      return false;
+    if (!FIT) scale = std::max(scale, (int)s.scale);
     if (s.num_kernels < 0 || s.param_offset < 0) return false;
     if ((long long)s.param_offset + s.num_kernels > rows) return false;
     if (s.kernel_offset != k || s.tile_offset != t || s.pixel_offset != px) return false;
     k += s.num_kernels;
     t += raster_tiles(s.width, s.height, s.origin_x, s.origin_y);
     px += (long long)s.width * s.height;
-    scale = std::max(scale, (int)s.scale);
   }
   if (t >= (1LL << 31) || k * 16 >= (1LL << 31)) return false;
-  *T = (int)t;
-  *K = (int)k;
-  *max_scale = scale;
+  S->T = (int)t;
+  S->K = (int)k;
+  S->max_scale = scale;
   return true;
 }
 
@@ -128,8 +133,7 @@ bool batch_segs(const smoe_batch* b, Segs* out) {
     return false;
   Segs S;
   std::memset(&S, 0, sizeof(S));
-  if (!check_segments(b->segments_host, b->num_segments, b->num_params_rows, &S.T, &S.K,
-                      &S.max_scale))
+  if (!check_segments<false>(b->segments_host, b->num_segments, b->num_params_rows, &S))
     return false;
   S.tab = b->segments;
   S.n = b->num_segments;
@@ -202,14 +206,7 @@ bool fit_segs(const smoe_fit_state* st, Segs* S) {
         !valid_box(st->grid.box) || !valid_mode(st->grid.mode) || !valid_trunc(st->grid.trunc))
       return false;
     std::memset(S, 0, sizeof(*S));
-    if (!check_segments(st->segments_host, st->num_segments, st->K, &S->T, &S->K, &S->max_scale))
-      return false;
-    for (int i = 0; i < st->num_segments; ++i) {
-      const smoe_segment& s = st->segments_host[i];
-      if (s.scale != 1 || s.origin_x != 0 || s.origin_y != 0 ||
-          s.param_offset != s.kernel_offset || !no_sharpen(s.sharpen))
-        return false;
-    }
+    if (!check_segments<true>(st->segments_host, st->num_segments, st->K, S)) return false;
     if (S->K != st->K) return false;
     S->tab = st->segments;
     S->n = st->num_segments;

@@ -34,7 +34,7 @@ __host__ __device__ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 // The rasters of one call.  A batched call (several images of a batched fit, or several
 // render requests) numbers the blocks of all its rasters consecutively (segment s owns
 // blocks [tile_offset, tile_offset + T_s)) and its kernel rows likewise; each kernel and
-// each block then finds its segment by a binary search on those offsets.  A single-raster
+// each block then finds its segment by a search on those offsets (find_segment).  A single-raster
 // call has no table (tab == null) and uses `one`.
 struct Segs {
   const smoe_segment* __restrict__ tab;  // device table of n segments, or null

@@ -56,24 +56,26 @@ __global__ __launch_bounds__(kWave * WAVES) void k_backward(BackwardArgs a) {
       t[i] = ref[p];
     }
   }
+  bool hole = false;
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) {
-    PixelSeed<C> sd;
-    sd.gy = 0.0f;
-#pragma unroll
-    for (int c = 0; c < C; ++c) sd.g[c] = 0.0f;
+    PixelSeed<C> sd = hole_seed<C>();
     if (D[i] > 0.0f) {
       const float invD = RBF ? 1.0f : __builtin_amdgcn_rcpf(D[i]);
+      float gy = 0.0f;
 #pragma unroll
       for (int c = 0; c < C; ++c) {
         const float g = a.target ? (y[i].v[c] - t[i].v[c]) * inv_n2 : t[i].v[c];
-        if (!RBF) sd.gy = __builtin_fmaf(g, y[i].v[c], sd.gy);
+        if (!RBF) gy = __builtin_fmaf(g, y[i].v[c], gy);
         sd.g[c] = g * invD;
       }
-      sd.gy = sd.gy * invD;
+      sd.gy = live_gy(gy * invD);
+    } else {
+      hole = true;
     }
     seeds[((lane >> 4) + 4 * (i + ROWS * wave_index<WAVES>())) * kTile + (lane & 15)] = sd;
   }
+  note_holes<WAVES>(sc, hole);
   const float2 o = block_base(sg, tile - sg.tile_offset);
   backward_accumulate<C, ORDER, false, WAVES>(block_box(sg, tile - sg.tile_offset), o.x, o.y, sg.inv_s,
                                        a.S.r, a.S.r2, a.records, a.vals, 0, false, a.ranges[tile],

@@ -156,17 +156,19 @@ void k_fit_tile(FitTileArgs a) {
     load_target();
   }
   float err[ROWS];
+  bool hole = false;
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) {
     err[i] = 0.0f;
-    PixelSeed<C> sd;
-    sd.gy = 0.0f;
+    PixelSeed<C> sd = hole_seed<C>();
+    const bool cov = in[i] && D[i] > 0.0f;
+    hole = hole || !cov;
 #pragma unroll
-    for (int c = 0; c < C; ++c) sd.g[c] = y[i].v[c] = 0.0f;
+    for (int c = 0; c < C; ++c) y[i].v[c] = 0.0f;
     if (in[i]) {
-      const bool cov = D[i] > 0.0f;
       // 1/D by v_rcp_f32 (1 ulp); y = N / D refined from it, as in the render
       const float invD = RBF ? 1.0f : (cov ? __builtin_amdgcn_rcpf(D[i]) : 0.0f);
+      float gy = 0.0f;
 #pragma unroll
       for (int c = 0; c < C; ++c) {
         // Eq. (2)-(4): y = N / D; Eq. (1): y = N
@@ -176,14 +178,15 @@ void k_fit_tile(FitTileArgs a) {
         err[i] = __builtin_fmaf(d, d, err[i]);
         if (cov) {
           const float g = d * inv_n2;
-          if (!RBF) sd.gy = __builtin_fmaf(g, yc, sd.gy);
+          if (!RBF) gy = __builtin_fmaf(g, yc, gy);
           sd.g[c] = g * invD;
         }
       }
-      sd.gy = sd.gy * invD;
+      if (cov) sd.gy = live_gy(gy * invD);
     }
     seeds[((lane >> 4) + 4 * (i + ROWS * wave)) * kTile + (lane & 15)] = sd;
   }
+  note_holes<WAVES>(sc, hole);
   if (a.image) {
     PixelValue<C>* img = reinterpret_cast<PixelValue<C>*>(a.image) + bp.base;
     float* den = a.denom + bp.base;

@@ -56,7 +56,6 @@ __global__ __launch_bounds__(kWave * WAVES) void k_backward(BackwardArgs a) {
       t[i] = ref[p];
     }
   }
-  bool hole = false;
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) {
     PixelSeed<C> sd = hole_seed<C>();
@@ -70,12 +69,9 @@ __global__ __launch_bounds__(kWave * WAVES) void k_backward(BackwardArgs a) {
         sd.g[c] = g * invD;
       }
       sd.gy = live_gy(gy * invD);
-    } else {
-      hole = true;
     }
     seeds[((lane >> 4) + 4 * (i + ROWS * wave_index<WAVES>())) * kTile + (lane & 15)] = sd;
   }
-  note_holes<WAVES>(sc, hole);
   const float2 o = block_base(sg, tile - sg.tile_offset);
   backward_accumulate<C, ORDER, false, WAVES>(block_box(sg, tile - sg.tile_offset), o.x, o.y, sg.inv_s,
                                        a.S.r, a.S.r2, a.records, a.vals, 0, false, a.ranges[tile],

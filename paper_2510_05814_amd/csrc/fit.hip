@@ -156,13 +156,11 @@ void k_fit_tile(FitTileArgs a) {
     load_target();
   }
   float err[ROWS];
-  bool hole = false;
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) {
     err[i] = 0.0f;
     PixelSeed<C> sd = hole_seed<C>();
     const bool cov = in[i] && D[i] > 0.0f;
-    hole = hole || !cov;
 #pragma unroll
     for (int c = 0; c < C; ++c) y[i].v[c] = 0.0f;
     if (in[i]) {
@@ -186,7 +184,6 @@ void k_fit_tile(FitTileArgs a) {
     }
     seeds[((lane >> 4) + 4 * (i + ROWS * wave)) * kTile + (lane & 15)] = sd;
   }
-  note_holes<WAVES>(sc, hole);
   if (a.image) {
     PixelValue<C>* img = reinterpret_cast<PixelValue<C>*>(a.image) + bp.base;
     float* den = a.denom + bp.base;

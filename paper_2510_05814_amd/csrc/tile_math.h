@@ -640,9 +640,10 @@ __device__ __forceinline__ float block_error(const float (&err)[kStrips / WAVES]
 // With the seed 1/D -> 1 and
 // sum_c g_c y_c -> 0 the same backward is the adjoint of the un-normalised sum of Eq. (1):
 // then w = pi K is dy_c/dm_c and G = sum_c g_c m_c is dL/d(pi K).
-// A hole is a pixel where no gradient flows (D = 0 or outside the raster).  Zero seeds alone would
-// not keep it out: a kernel centred outside the raster may pass the range of binary32 there, and
-// 0 * inf is not zero.  Its gy is -0, which no other pixel's is (live_gy).
+// A hole is a pixel where no gradient flows (D = 0 or outside the raster).  Zero seeds do not
+// always keep it out: a kernel centred outside the raster may pass the range of binary32 there, and
+// 0 * inf is not zero.  Its gy is -0, which no other pixel's is (live_gy), for the backward's
+// second look.
 template <int C>
 struct alignas(C == 3 ? 16 : 8) PixelSeed {
   float g[C];
@@ -716,14 +717,7 @@ __device__ __forceinline__ EllipseBox ellipse_box(const BlockBox& bb, float r, f
 struct BackwardScratch {
   uint32_t ent[kChunk];  // the chunk's list entries, then packed boxes
   uint2 out[kChunk];     // (kernel id or staged record, partial row) in processing order
-  uint32_t holes[4];     // whether a wave's pixels have holes (PixelSeed), one word a wave
 };
-// Notes the holes among this wave's pixels (any: the lane has one).
-template <int WAVES>
-__device__ __forceinline__ void note_holes(BackwardScratch& sc, bool any) {
-  const bool holes = __any(any);
-  if ((threadIdx.x & 63) == 0) sc.holes[wave_index<WAVES>()] = holes;
-}
 
 // The partial row of a list entry (Backward, below) at position pos of the lists; list0: the
 // first position of its list.
@@ -832,10 +826,6 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
   for (int base = rg.x; base < rg.y; base += kChunk) {
     const int n = __builtin_amdgcn_readfirstlane(min(kChunk, rg.y - base));
     __syncthreads();
-    uint32_t any = sc.holes[0];
-#pragma unroll
-    for (int w = 1; w < WAVES; ++w) any |= sc.holes[w];
-    const bool holes = __builtin_amdgcn_readfirstlane(any) != 0;
     if (!laid_out) {
       if (wave == 0) {
         const uint32_t e = lane < n ? vals[base + lane] : 0u;
@@ -856,7 +846,11 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
       const uint2 out = sc.out[g + sub];
       const int M = __builtin_amdgcn_readfirstlane(bx >> 12);  // the group's first has the most
       float tot = 0.0f;
-      if (M > 0) {
+      // A first look at the group's pixels and, if a sum is no number, a second: 0 * inf may have
+      // come from a hole, or from a lane without a pixel and an infinite z1 or reciprocal.  (Flags
+      // asked in the first look cost every group: 2048^2 fit step 109.8 -> 111.5 us with them, 108.6
+      // -> 109.3 with this.)
+      for (bool careful = false; M > 0; careful = true) {
         float r[RS];
         load_record<RS>(r, staged ? staged + out.x * Q
                                   : reinterpret_cast<const float4*>(records + (size_t)out.x * RS));
@@ -868,7 +862,7 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
         const float hstep = (float)(1 << lr);
         const float xc = x0 + (float)col;
         const float dx = (UNIT ? xc : xc * inv_s) - r[0];
-        const float z1 = dx * r[2];
+        float z1 = dx * r[2];
         const float tt = r[3] * z1;
         const float zz1 = z1 * z1;
         // a_c + wx_c dx: the expert's value along the lane's column
@@ -881,9 +875,7 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
 #pragma unroll
         for (int c = 0; c < C; ++c) A[c] = Y[c] = 0.0f;
         float V = 0.0f, S2 = 0.0f, R = 0.0f;
-        // (a loop of its own where the block has holes: with a uniform branch inside, the 2048^2 fit
-        // step took 112.5 us instead of 110.1; it was 109.6 with nothing kept out)
-        auto walk = [&](auto with_holes) {
+        auto walk = [&](auto second_look) {
           for (int m = 0; m < M; ++m) {
             if (m < mine) {
               // both steps' seeds are loaded and tests made before the first is used
@@ -902,7 +894,7 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
               sp += (2 * kTile) << lr;
 #pragma unroll
               for (int i = 0; i < 2; ++i) {
-                if (q[i] <= r2 && !(with_holes && sd[i].hole())) {
+                if (q[i] <= r2 && !(second_look && sd[i].hole())) {
                   const float ek = __builtin_amdgcn_exp2f(__builtin_fmaf(q[i], -0.5f * kLog2e, r[5]));
                   const float ed = ek * dy[i];
                   float Gs = -sd[i].gy;  // G / D
@@ -923,8 +915,15 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
             }
           }
         };
-        if (holes) walk(std::true_type{});
-        else walk(std::false_type{});
+        if (careful) {
+          walk(std::true_type{});
+          if (R == 0.0f && V == 0.0f && S2 == 0.0f) {  // nothing for z1 and the reciprocals to scale
+            z1 = 0.0f;
+            r[2] = r[4] = r[6] = 0.0f;
+          }
+        } else {
+          walk(std::false_type{});
+        }
         const float B2 = -V * r[4];
         const float B1 = -__builtin_fmaf(r[6], B2, z1 * R);
         float acc[16];
@@ -945,6 +944,7 @@ __device__ __forceinline__ void backward_accumulate(const BlockBox& bb, float x0
 #pragma unroll
         for (int i = 6 + C * (1 + 2 * ORDER); i < 16; ++i) acc[i] = 0.0f;
         tot = row_reduce16_masked(acc);
+        if (careful || !__any(tot != tot)) break;
       }
       if (g + sub < n && l16 < PS) pair_grads[(size_t)out.y * PS + l16] = tot;
     }

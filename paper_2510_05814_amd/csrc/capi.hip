@@ -548,6 +548,11 @@ smoe_status smoe_read_status(const smoe_bins* bins, int32_t* out4, void* stream)
   if (!bins || !bins->status) return SMOE_ERR_INVALID;
   int32_t h[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   hipStream_t s = static_cast<hipStream_t>(stream);
+  // A stream under capture cannot be waited for, and the copy would be recorded, with this call's
+  // stack as its target: refused before anything is issued.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
+    return SMOE_ERR_HIP;
   // one copy on the stream, one wait
   if (hipMemcpyAsync(h, bins->status, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)

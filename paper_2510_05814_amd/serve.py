@@ -179,6 +179,22 @@ def admit(pending, in_use: int, budget: int, footprint, max_batch: int, max_pixe
     return batch
 
 
+WAIT, NOW, BEHIND = 0, 1, 2
+
+
+def issue(inflight: int, inflight_blocks: int, waiting: int, last: bool, fill_blocks: int,
+          overlap_backlog: int) -> int:
+    """Whether a batch of the `waiting` requests is issued: NOW (beside the batches in flight,
+    if any), BEHIND the one in flight, or not yet (WAIT).  last: no request is still to arrive.
+    While the batches in flight leave part of the GPU idle, one is issued if none is in flight or a
+    backlog has formed.  A batch that fills the GPU runs alone; once every request has arrived,
+    waiting for its end gains the next batch no company, so that one is issued behind it and the
+    device goes from one to the other without the host in between."""
+    if inflight_blocks < fill_blocks:
+        return NOW if not inflight or waiting >= overlap_backlog else WAIT
+    return BEHIND if last and inflight == 1 else WAIT
+
+
 def _tiles(w: int, h: int, ox: int = 0, oy: int = 0) -> int:
     """Blocks of a raster (16x16 blocks of the output grid aligned to multiples of 16)."""
     return ((ox + w - 1) // TILE - ox // TILE + 1) * ((oy + h - 1) // TILE - oy // TILE + 1)
@@ -377,7 +393,8 @@ class Server:
         """fill_blocks: a further batch is started beside those in flight only while they
         hold fewer 16x16 blocks than this -- about half of what the GPU renders at once
         (256 CUs x 4 SIMDs x 7-8 one-wave blocks).  A batch that fills the GPU runs alone;
-        requests that arrive meanwhile queue and leave together in the next batch.
+        requests that arrive meanwhile queue and leave together in the next batch, which is
+        issued to start when that one ends if no further request is to arrive.
         overlap_backlog: a batch is started beside one in flight only when at least this many
         requests wait; a lone request waits for the batch in flight instead (measured: at
         light load, overlapping a lone request lengthens the tail of the larger renders).
@@ -546,16 +563,13 @@ class Server:
                     sl.batch = None
                     free.append(si)
                     inflight -= 1
-            # Once every request has arrived, waiting for a batch that fills the GPU gains no
-            # company: the next one is issued behind it, so that the device goes from one to
-            # the other without the host in between.
-            last = nxt == len(order)
-            while free and pending and (
-                    (inflight_blocks < self.fill_blocks
-                     and (not inflight or len(pending) >= self.overlap_backlog))
-                    or (last and inflight == 1)):
+            while free and pending:
+                how = issue(inflight, inflight_blocks, len(pending), nxt == len(order),
+                            self.fill_blocks, self.overlap_backlog)
+                if not how:
+                    break
                 after = None
-                if inflight_blocks >= self.fill_blocks:
+                if how == BEHIND:
                     after = next(sl.batch for sl in self.slots if sl.batch is not None)
                 if len(pending) == 1:  # the common case at low load
                     k, t, p, _, need = pending[0]._smoe_info

@@ -155,13 +155,16 @@ __global__ __launch_bounds__(256) void k_preprocess(int C, int order,
 }
 
 // Exclusive scan of the per-block counts into [begin, end) ranges, with P, the overflow flag
-// and the longest list into status.  A workgroup takes kScanChunk consecutive blocks, four
-// counts a thread; no workgroup waits for another.  What lies before its chunk, and the total
-// (on an overflow every range is written empty), each workgroup sums for itself: from all the
-// counts (part null), or from the chunks' sums that k_scan_sums left in part.  Summing all
-// the counts is quadratic in the number of chunks, so it serves up to kScanDirect blocks
-// (4096^2 pixels: 256 KB read by each of 16 workgroups), where it saves a launch.  One
-// workgroup that walked all chunks took 7.7 us at 16384 blocks and 107 us for the 220 000 of a
+// and the longest list into status.  A chunk is kScanChunk consecutive blocks, four counts a
+// thread; a workgroup takes one chunk, or `per` of them in turn; none waits for another.  What lies
+// before its chunks, and the total (on an overflow every range is written empty), each workgroup
+// sums for itself: from all the counts (part null), or from the chunks' sums that k_scan_sums
+// left in part.  With a workgroup to a chunk, summing all the counts is quadratic in their number,
+// so it serves up to kScanDirect blocks (4096^2 pixels: 256 KB read by each of 16 workgroups),
+// where it saves a launch; beyond, where the storage has no room for the chunks' sums, by
+// kScanDirect / kScanChunk workgroups (binning of 65536^2 with room for 4096 pairs: 25.4 ms by a
+// workgroup a chunk, 11.1 by a single one for all, 3.4 by sixteen).
+// One workgroup that walked all chunks took 7.7 us at 16384 blocks and 107 us for the 220 000 of a
 // batch of serving requests; the two kernels take 5.6 + 4.6 us there, the direct one 6.8 us at
 // 16384 blocks.  The batch of twelve requests 1569 -> 1469 us.
 constexpr int kScanThreads = 1024, kScanChunk = 4 * kScanThreads, kScanDirect = 65536;
@@ -213,15 +216,14 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_sums(int T,
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan(int T, const int32_t* __restrict__ counts,
-                                                       const int4* __restrict__ part,
+                                                       const int4* __restrict__ part, int per,
                                                        int2* __restrict__ ranges, int capacity,
                                                        int32_t* __restrict__ status) {
-  __shared__ long long s_wave[kScanThreads / 64];
+  __shared__ long long s_wave[2][kScanThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int base = blockIdx.x * kScanChunk;
-  const int4 c = four_counts(counts, base + 4 * tid, T);
+  const long long first = (long long)blockIdx.x * per * kScanChunk;  // (the last may pass T)
   ChunkTotals t{0, 0, 0};
-  if (part) {
+  if (part) {  // (one chunk a workgroup)
     for (int b = tid; b < (int)gridDim.x; b += kScanThreads) {
       const int4 p = part[b];
       const long long sum = (long long)(uint32_t)p.x | (long long)p.y << 32;
@@ -234,32 +236,40 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(int T, const int32_t* __r
       const int4 v = four_counts(counts, q, T);
       const long long sum = (long long)v.x + v.y + v.z + v.w;
       t.total += sum;
-      if (q < base) t.before += sum;
+      if (q < first) t.before += sum;
       t.longest = max(t.longest, max(max(v.x, v.y), max(v.z, v.w)));
     }
   }
   t = workgroup_totals(t);
   const bool over = t.total > (long long)capacity;
-  // the thread's place in its chunk
-  const long long mine = (long long)c.x + c.y + c.z + c.w;
-  long long incl = mine;
+  for (int k = 0; k < per && first + (long long)k * kScanChunk < T; ++k) {
+    const int base = (int)(first + (long long)k * kScanChunk);
+    const int4 c = four_counts(counts, base + 4 * tid, T);
+    // the thread's place in its chunk
+    const long long mine = (long long)c.x + c.y + c.z + c.w;
+    long long incl = mine;
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const long long o = __shfl_up(incl, off);
-    if (lane >= off) incl += o;
-  }
-  if (lane == 63) s_wave[wave] = incl;
-  __syncthreads();
-  long long begin = t.before + incl - mine;
-  for (int w = 0; w < wave; ++w) begin += s_wave[w];
-  // (ranges fit in int32 whenever they are written: P is then at most the int32 capacity)
-  const int n[4] = {c.x, c.y, c.z, c.w};
-  int b = (int)begin;
+    for (int off = 1; off < 64; off <<= 1) {
+      const long long o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    if (lane == 63) s_wave[k & 1][wave] = incl;
+    __syncthreads();  // (the one barrier a chunk: the next writes the other half)
+    long long begin = t.before + incl - mine;
+    for (int w = 0; w < kScanThreads / 64; ++w) {
+      const long long n = s_wave[k & 1][w];
+      if (w < wave) begin += n;
+      t.before += n;
+    }
+    // (ranges fit in int32 whenever they are written: P is then at most the int32 capacity)
+    const int n[4] = {c.x, c.y, c.z, c.w};
+    int b = (int)begin;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int i = base + 4 * tid + k;
-    if (i < T) ranges[i] = over ? make_int2(0, 0) : make_int2(b, b + n[k]);
-    b += n[k];
+    for (int i = 0; i < 4; ++i) {
+      const int at = base + 4 * tid + i;
+      if (at < T) ranges[at] = over ? make_int2(0, 0) : make_int2(b, b + n[i]);
+      b += n[i];
+    }
   }
   if (blockIdx.x == 0 && tid == 0) {
     status[0] = (int)min(t.total, (long long)INT32_MAX);
@@ -749,8 +759,10 @@ hipError_t launch_scan(const Segs& S, const smoe_bins& b, hipStream_t s) {
     part = reinterpret_cast<int4*>(b.keys);
     k_scan_sums<<<chunks, kScanThreads, 0, s>>>(S.T, b.tile_counts, part);
   }
-  k_scan<<<chunks, kScanThreads, 0, s>>>(S.T, b.tile_counts, part,
-                                         reinterpret_cast<int2*>(b.ranges), b.capacity, b.status);
+  const int per = part ? 1 : cdiv(chunks, kScanDirect / kScanChunk);
+  k_scan<<<cdiv(chunks, per), kScanThreads, 0, s>>>(S.T, b.tile_counts, part, per,
+                                                    reinterpret_cast<int2*>(b.ranges), b.capacity,
+                                                    b.status);
   return hipGetLastError();
 }
 

@@ -27,10 +27,8 @@ namespace {
 // 13.6 / 45.9; k_preprocess at 3024 rows 7.8 / 6.7 / 11.0, at 65536 rows 12.6 / 21.5 / 70, at 4000
 // rows of 150 blocks each 57 / 37 / 38.  Rows of a few blocks have nothing to share out: four
 // (few_blocks; k_scatter_fixed over 66564 rows of a block each 11.3 against 24.6).  k_scatter
-// reads the rectangle: sixteen always (65536
-// rows 9.6 / 9.5 / 36, a batch of serving requests 108 / 71 / 140, the 4000 wide rows 104 /
-// 53 / 37).
-constexpr int kScatterLanes = 16, kManyKernels = 16384;
+// follows the same rule; its four lanes share out only what is short.
+constexpr int kManyKernels = 16384;
 // Calls f(std::integral_constant<int, LANES>) for the kernel rows of S.
 template <class F>
 inline void with_lanes(const Segs& S, F&& f) {
@@ -279,11 +277,17 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(int T, const int32_t* __r
   }
 }
 
-// Lane q of a kernel's group appends the kernel id to the buckets of the kernel's covered
-// blocks q, q + 16, ... (row-major inside its block rectangle; rects: tile_rects, or (SHARED)
+// Lane q of a kernel's LANES lanes appends the kernel id to the buckets of the kernel's covered
+// blocks q, q + LANES, ... (row-major inside its block rectangle; rects: tile_rects, or (SHARED)
 // native_rects).  A lane's appends go out four at
 // a time: each waits for its atomic's result only when all four are on their way.
-template <bool SHARED>
+// Four lanes: of a row's first sixteen blocks; the sixteen lanes of four rows take the
+// further blocks of each row together.  Measured, the whole binning with sixteen lanes a row / with
+// four to the end of the row / with this: 65536 ordered rows of 6.6 blocks on 1024^2 87 / 60 / 59 us
+// (in random order 65.5 / 70 / 70), 262144 on 2048^2 201 / 134 / 133, 20000 rows of 69 blocks 100 /
+// 130 / 107; 4096 rows of 5.6 blocks 18.1 / 19.0 and 4000 of 117 blocks 72 / 178: with_lanes gives
+// them sixteen.
+template <int LANES, bool SHARED>
 __global__ __launch_bounds__(256) void k_scatter(Segs S, const int4* __restrict__ rects,
                                                  const int2* __restrict__ ranges,
                                                  int32_t* __restrict__ cursors,
@@ -291,20 +295,16 @@ __global__ __launch_bounds__(256) void k_scatter(Segs S, const int4* __restrict_
                                                  const int32_t* __restrict__ status) {
   constexpr int AHEAD = 4;
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-  const int g = gid / kScatterLanes, q0 = gid % kScatterLanes;
-  if (g >= S.K || status[1] != 0) return;
-  const int j = binning_kernel(g, S.K);
-  const int4 rc = rects[j];
-  const int n = rect_count(rc);
-  if (q0 >= n) return;
-  const SegGrid sg = seg_of_kernel(S, j);
-  const int w = rc.z - rc.x + 1;
-  for (int q = q0; q < n; q += AHEAD * kScatterLanes) {
+  const int g = gid / LANES, q0 = gid % LANES;
+  if (status[1] != 0) return;
+  // the row's blocks q, q + stride, ... below n, AHEAD of them
+  auto append = [&](const SegGrid& sg, int j, int4 rc, int n, int q, int stride) {
+    const int w = rc.z - rc.x + 1;
     int pos[AHEAD];
     int2 rg[AHEAD];
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k) {
-      const int p = q + k * kScatterLanes;
+      const int p = q + k * stride;
       if (p < n) {
         const int t = covered_block<SHARED>(sg, rc.x + p % w, rc.y + p / w);
         pos[k] = atomicSub(&cursors[t], 1) - 1;  // the block's count runs down to zero
@@ -313,8 +313,34 @@ __global__ __launch_bounds__(256) void k_scatter(Segs S, const int4* __restrict_
     }
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k)
-      if (q + k * kScatterLanes < n && pos[k] >= 0 && rg[k].x + pos[k] < rg[k].y)
+      if (q + k * stride < n && pos[k] >= 0 && rg[k].x + pos[k] < rg[k].y)
         vals[rg[k].x + pos[k]] = (uint32_t)j;
+  };
+  int4 rc = make_int4(0, 0, -1, -1);
+  int j = 0;
+  if (g < S.K) {
+    j = binning_kernel(g, S.K);
+    rc = rects[j];
+  }
+  const int n = rect_count(rc);
+  constexpr int FIRST = LANES * AHEAD;
+  if (q0 < n) {
+    const SegGrid sg = seg_of_kernel(S, j);
+    for (int q = q0; q < (LANES == 16 ? n : min(n, FIRST)); q += FIRST)
+      append(sg, j, rc, n, q, LANES);
+  }
+  if (LANES == 16) return;
+  // (the lanes of a group of sixteen stay together here: n of a row is the same for them)
+  static_assert(LANES == 16 || FIRST == 16, "the rest begins with block 16");
+#pragma unroll 1
+  for (int r = 0; r < 16 / LANES; ++r) {
+    const int from = r * LANES, nr = __shfl(n, from, 16);
+    if (nr <= FIRST) continue;
+    const int jr = __shfl(j, from, 16);
+    const int4 rr = make_int4(__shfl(rc.x, from, 16), __shfl(rc.y, from, 16),
+                              __shfl(rc.z, from, 16), __shfl(rc.w, from, 16));
+    const SegGrid sg = seg_of_kernel(S, jr);
+    for (int q = FIRST + (threadIdx.x & 15); q < nr; q += 16 * AHEAD) append(sg, jr, rr, nr, q, 16);
   }
 }
 
@@ -788,16 +814,18 @@ hipError_t launch_scatter_fixed(const Segs& S, const smoe_bins& b, const float* 
 }
 
 hipError_t launch_scatter(const Segs& S, const smoe_bins& b, hipStream_t s) {
-  if (S.K > 0) {
-    const int groups = cdiv((long long)S.K * kScatterLanes, 256);
-    const int2* ranges = reinterpret_cast<const int2*>(b.ranges);
+  if (S.K == 0) return hipSuccess;
+  const int2* ranges = reinterpret_cast<const int2*>(b.ranges);
+  with_lanes(S, [&](auto lanes) {
+    constexpr int L = decltype(lanes)::value;
+    const int groups = cdiv((long long)S.K * L, 256);
     if (shared_lists(S))
-      k_scatter<true><<<groups, 256, 0, s>>>(S, reinterpret_cast<const int4*>(b.native_rects),
-                                             ranges, b.tile_counts, b.vals_alt, b.status);
+      k_scatter<L, true><<<groups, 256, 0, s>>>(S, reinterpret_cast<const int4*>(b.native_rects),
+                                                ranges, b.tile_counts, b.vals_alt, b.status);
     else
-      k_scatter<false><<<groups, 256, 0, s>>>(S, reinterpret_cast<const int4*>(b.tile_rects),
-                                              ranges, b.tile_counts, b.vals, b.status);
-  }
+      k_scatter<L, false><<<groups, 256, 0, s>>>(S, reinterpret_cast<const int4*>(b.tile_rects),
+                                                 ranges, b.tile_counts, b.vals, b.status);
+  });
   return hipGetLastError();
 }
 

@@ -428,7 +428,7 @@ __global__ __launch_bounds__(256) void k_spread_counts(Segs S, int32_t* __restri
 }
 
 // Orders every block's list by kernel id, writes the block-id keys and clears the block's
-// counter.  A wave per block ranks a list of up to 64 ids in registers; a longer one is then
+// counter.  A wave per block ranks a list of up to kRankList ids; a longer one is then
 // taken by the workgroup's four waves together (sort_long).  SHARED: the entries stand, in any
 // order, in vals_alt at the place of the native block's first block, which nothing here
 // writes; each block ranks them into its own place (its keys' place is the scratch then).
@@ -440,8 +440,7 @@ __global__ __launch_bounds__(64 * kSortBlocks) void k_sort_buckets(Segs S,
                                                                    uint32_t* __restrict__ vals_alt,
                                                                    uint32_t* __restrict__ keys,
                                                                    int32_t* __restrict__ cursors) {
-  __shared__ __align__(16) uint32_t s_rank[kSortBlocks][64];
-  __shared__ LongSortScratch<kSortBlocks, 32768> s_long;
+  __shared__ __align__(16) LongSortScratch<kSortBlocks, 32768, 2048> s_long;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int t0 = blockIdx.x * kSortBlocks, t = t0 + wave, T = S.T;
   // the workgroup's ranges, one to a lane: a load in front of each list's turn below would be
@@ -454,22 +453,26 @@ __global__ __launch_bounds__(64 * kSortBlocks) void k_sort_buckets(Segs S,
     const int2 rg = range(wave);
     const int n = rg.y - rg.x;
     if (lane == 0) cursors[t] = 0;
-    if (SHARED) {
-      if (n > 0 && n <= 64) {
-        const uint32_t* from = vals_alt + ranges[counted_block(S, t)].x;
+    // (a quarter of s_long a wave: sort_long writes there only after a barrier of all four)
+    uint32_t* s_rank = s_long.run + wave * kRankList;
+    if (n > 0 && n <= kRankList) {
+      const uint32_t* from = SHARED ? vals_alt + ranges[counted_block(S, t)].x : vals + rg.x;
+      if (n <= 64) {
         const uint32_t e = lane < n ? from[lane] : 0xFFFFFFFFu;
-        const int rank = rank64(e, n, s_rank[wave]);
+        const int rank = rank64(e, n, s_rank);
         if (lane < n) {
           vals[rg.x + rank] = e;
           keys[rg.x + lane] = (uint32_t)t;
         }
+      } else {
+        rank_list<64>(from, vals + rg.x, n, s_rank, lane, wave_sync);
+        for (int i = lane; i < n; i += 64) keys[rg.x + i] = (uint32_t)t;
       }
-    } else {
+    } else if (!SHARED) {
       for (int i = lane; i < n; i += 64) keys[rg.x + i] = (uint32_t)t;
-      if (n > 0 && n <= 64) rank_sort64(vals + rg.x, n, s_rank[wave]);
     }
   }
-  for (uint64_t left = __ballot(mine.y - mine.x > 64); left != 0; left &= left - 1) {
+  for (uint64_t left = __ballot(mine.y - mine.x > kRankList); left != 0; left &= left - 1) {
     const int k = __builtin_ctzll(left);
     const int2 rg = range(k);
     const int n = rg.y - rg.x;

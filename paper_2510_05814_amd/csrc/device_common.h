@@ -165,35 +165,121 @@ __device__ __forceinline__ int rank64(uint32_t e, int n, uint32_t* __restrict__ 
   return rank;
 }
 
-// Sorts a list of n <= 64 distinct entries seg[0, n) ascending with one wave.
-__device__ __forceinline__ void rank_sort64(uint32_t* __restrict__ seg, int n,
-                                            uint32_t* __restrict__ scratch) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t e = lane < n ? seg[lane] : 0xFFFFFFFFu;
-  const int rank = rank64(e, n, scratch);
-  if (lane < n) seg[rank] = e;
+// Orders a list of n <= kRankList distinct entries from[0, n) into to[0, n) (which may be from) with NT
+// threads, of which the caller is number tid: an entry's place is the number of entries below it,
+// counted as in rank64.  lds: kRankList u32, 16-byte aligned; sync: a barrier of the NT threads.
+// A bitmap of the ids (sort_long) costs a workgroup about 1.7 us a window whatever n is: binning of
+// 262144 kernels at 2048^2 (lists of about 105) with bitmaps from 65 entries on 133 us, and 237 if
+// the kernels are in random order (eight windows); with this up to 128 / 192 / 256 entries 124 / 121 /
+// 121 and 136 / 119 / 119, but lists of up to 518 at scale 3 102 / 102 / 108.
+constexpr int kRankList = 192;
+template <int NT, class Sync>
+__device__ __forceinline__ void rank_list(const uint32_t* from, uint32_t* to, int n,
+                                          uint32_t* __restrict__ lds, int tid, Sync&& sync) {
+  for (int i = tid; i < ((n + 3) & ~3); i += NT) lds[i] = i < n ? from[i] : 0xFFFFFFFFu;
+  sync();
+  const uint4* l4 = reinterpret_cast<const uint4*>(lds);
+  for (int i = tid; i < n; i += NT) {
+    const uint32_t e = lds[i];
+    int rank = 0;
+    for (int j = 0; j < (n + 3) >> 2; ++j) {
+      const uint4 q = l4[j];
+      rank += (q.x < e ? 1 : 0) + (q.y < e ? 1 : 0) + (q.z < e ? 1 : 0) + (q.w < e ? 1 : 0);
+    }
+    to[rank] = e;
+  }
+  sync();
 }
 
-// Scratch of sort_long: a bitmap over a window of kernel ids and, per word, the ids below it.
-template <int WAVES, int WINDOW_>
+// Scratch of sort_long: a bitmap over a window of kernel ids and, per word, the ids below it; or a
+// run of entries.
+template <int WAVES, int WINDOW_, int RUN_>
 struct LongSortScratch {
-  static constexpr int WINDOW = WINDOW_;
-  uint32_t bits[WINDOW / 32];
-  uint32_t below[WINDOW / 32];
+  static constexpr int WINDOW = WINDOW_, RUN = RUN_;
+  union {
+    struct {
+      uint32_t bits[WINDOW / 32];
+      uint32_t below[WINDOW / 32];
+    };
+    uint32_t run[RUN];
+  };
   uint32_t wave[WAVES], lo[WAVES], hi[WAVES];
 };
 
-// Orders a list of n > 64 entries seg[0, n) by kernel id (entry >> shift; the ids are distinct)
-// with a workgroup of WAVES waves, through alt[0, n): an entry's place is the number of ids
-// below its own, which a bitmap of the ids present gives -- one pass to set the bits, one over
-// the words for the running counts, one to place the entries -- for every window of
+// Orders distinct entries seg[0, n) ascending with NT threads, through alt[0, n): a bitonic sort of
+// each run of RUN entries in LDS, then merges of pairs of runs, in which an entry's place is its
+// index in its own run plus the number of smaller entries in the other.
+template <int NT, int RUN>
+__device__ __forceinline__ void sort_runs(uint32_t* seg, uint32_t* alt, int n,
+                                          uint32_t* __restrict__ run) {
+  const int tid = threadIdx.x;
+  for (int c0 = 0; c0 < n; c0 += RUN) {
+    const int m = min(RUN, n - c0);
+    int p2 = 2;
+    while (p2 < m) p2 <<= 1;
+    for (int i = tid; i < p2; i += NT) run[i] = i < m ? seg[c0 + i] : 0xFFFFFFFFu;
+    __syncthreads();
+    for (int k = 2; k <= p2; k <<= 1) {
+      for (int j = k >> 1; j > 0; j >>= 1) {
+        for (int i = tid; i < p2 >> 1; i += NT) {
+          const int a = 2 * i - (i & (j - 1)), b = a + j;
+          const uint32_t x = run[a], y = run[b];
+          if ((x > y) == ((a & k) == 0)) {
+            run[a] = y;
+            run[b] = x;
+          }
+        }
+        __syncthreads();
+      }
+    }
+    for (int i = tid; i < m; i += NT) seg[c0 + i] = run[i];
+    __threadfence_block();
+    __syncthreads();
+  }
+  uint32_t *src = seg, *dst = alt;
+  for (int width = RUN; width < n; width <<= 1) {
+    for (int i = tid; i < n; i += NT) {
+      const int own = i / width * width;               // begin of the entry's run
+      const bool left = (own / width & 1) == 0;
+      const int other = left ? own + width : own - width;
+      const uint32_t v = src[i];
+      int lo = min(other, n), hi = min(other + width, n);
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (src[mid] < v) lo = mid + 1;
+        else hi = mid;
+      }
+      dst[min(own, other) + (i - own) + (lo - min(other, n))] = v;
+    }
+    __threadfence_block();
+    __syncthreads();
+    uint32_t* t = src;
+    src = dst;
+    dst = t;
+  }
+  if (src != seg) {
+    for (int i = tid; i < n; i += NT) seg[i] = src[i];
+    __threadfence_block();
+    __syncthreads();
+  }
+}
+
+// Orders a list of n > kRankList entries seg[0, n) by kernel id (entry >> shift; the ids are
+// distinct) with a workgroup of WAVES waves, through alt[0, n).  Where the list's ids lie close
+// together, as they do in a model whose kernels' order follows the image, an entry's place is the
+// number of ids below its own, which a bitmap of the ids present gives -- one pass to set the bits,
+// one over the words for the running counts, one to place the entries -- for every window of
 // WINDOW ids between the list's least and greatest.  The work is proportional to n plus
 // the ids' span / 32, against n log^2 n for a sorting network by one wave, which took 97 us over
-// 1024 lists of 500 to 900 ids; this takes 18 us.
+// 1024 lists of 500 to 900 ids; this takes 18 us.  Ids spread over more than kRunWindows windows, in
+// a list that fits a run, go by sort_runs (a million kernels in random order at 2048^2, lists of up
+// to 360: binning 810 -> 437 us, fit step 1580 -> 1096); longer lists do where the windows would
+// outlast the merges.
 // All threads of the workgroup call it, with the same arguments; the result is in seg.
-template <int WAVES, int WINDOW>
-__device__ __forceinline__ void sort_long(uint32_t* __restrict__ seg, uint32_t* __restrict__ alt,
-                                          int n, int shift, LongSortScratch<WAVES, WINDOW>& sc) {
+constexpr uint32_t kRunWindows = 4, kMergeWindows = 64;
+template <int WAVES, int WINDOW, int RUN>
+__device__ __forceinline__ void sort_long(uint32_t* __restrict__ seg, uint32_t* __restrict__ alt, int n,
+                                          int shift, LongSortScratch<WAVES, WINDOW, RUN>& sc) {
   constexpr int NT = 64 * WAVES, WORDS = WINDOW / 32, PER = WORDS / NT;
   static_assert(WORDS % NT == 0, "whole words per thread");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -215,6 +301,11 @@ __device__ __forceinline__ void sort_long(uint32_t* __restrict__ seg, uint32_t* 
   for (int w = 0; w < WAVES; ++w) {
     lo = min(lo, sc.lo[w]);
     hi = max(hi, sc.hi[w]);
+  }
+  const uint32_t windows = (hi - lo) / WINDOW + 1;
+  if (windows > (n <= RUN ? kRunWindows : kMergeWindows)) {
+    sort_runs<NT, RUN>(seg, alt, n, sc.run);
+    return;
   }
   uint32_t done = 0;  // entries of the windows before
   for (uint32_t base = lo; base <= hi; base += WINDOW) {

@@ -46,12 +46,12 @@ __global__ __launch_bounds__(kWave * WAVES) __attribute__((amdgpu_waves_per_eu(W
 void k_fit_tile(FitTileArgs a) {
   constexpr int ROWS = kStrips / WAVES;
   constexpr int LDS_FLOATS = kChunk * record_stride(C, ORDER);
-  static_assert(LDS_FLOATS >= 64, "the rank sort's scratch lives in the record buffer");
+  static_assert(LDS_FLOATS >= kRankList, "the ranking's scratch lives in the record buffer");
   // The forward's records and the backward's pixel seeds: the one after the other in the same
   // place, so that eight one-wave blocks fit a SIMD's share of LDS; side by side with several
   // waves to a block, where the backward then reads its records from LDS.  (Before both, a
   // long bucket's sort.)
-  using LongSort = LongSortScratch<WAVES, 8192>;
+  using LongSort = LongSortScratch<WAVES, 8192, (LDS_FLOATS >= 1024 ? 1024 : 512)>;
   constexpr int REC_BYTES = LDS_FLOATS * 4, SEED_BYTES = kTilePixels * (int)sizeof(PixelSeed<C>);
   constexpr int SEED_AT = WAVES == 1 ? 0 : REC_BYTES;
   constexpr int LDS_BYTES =
@@ -128,6 +128,12 @@ void k_fit_tile(FitTileArgs a) {
     }
     __syncthreads();
     if (wave == 0 && lane < n) a.vals[rg.x + rank] = e;
+  } else if (n <= kRankList) {
+    rank_list<kWave * WAVES>(a.vals + rg.x, a.vals + rg.x, n, reinterpret_cast<uint32_t*>(srec),
+                             (int)threadIdx.x, [] {
+                               __threadfence_block();
+                               __syncthreads();
+                             });
   } else {
     sort_long(a.vals + rg.x, a.vals_alt + rg.x, n, a.shift, *reinterpret_cast<LongSort*>(srec));
   }

@@ -499,7 +499,11 @@ __global__ __launch_bounds__(64 * kSortBlocks) void k_sort_buckets(Segs S,
 // test, and a kernel that covers every block costs what any other does, where the counters'
 // atomics queue up.  What bounds it is the latency of its phases (loads, ballots, two
 // scans, stores), so the rectangles of four chunks are loaded ahead (at 16384 kernels and 4096
-// blocks 30.0 -> 24.4 us); the figures against the other binning are with the rule below.
+// blocks 30.0 -> 24.4 us) -- and, where the kernels' order does not follow the image and every chunk
+// has a few of every block's, the ballots and the chunks' turns at the end: ballots are gathered in
+// lanes and stored together, and a lane then writes its own chunk's few entries (16384 kernels in
+// random order on 1024x512 40.1 -> 26.6 us, in the image's order 22.3 -> 21.6; 4000 wide ones on
+// 512^2 18 -> 16).  The figures against the other binning are with the rule below.
 //
 // ROWS_TOO: a single workgroup takes all blocks, and each lane works its kernel's row out itself
 // (k_preprocess's work: one launch less).  Otherwise k_preprocess<MARK> has run, and a
@@ -522,6 +526,13 @@ struct ListArgs {
 };
 constexpr int kListWaves = 8, kListThreads = 64 * kListWaves, kListBlocks = kListWaves;
 constexpr int kListMasks = 2048;  // ballots a workgroup keeps (blocks x chunks of 64 kernels)
+
+// Lane LANE of (lo, hi) takes m (wave-uniform).
+template <int LANE>
+__device__ __forceinline__ void write_lane(uint64_t m, uint32_t& lo, uint32_t& hi) {
+  asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((uint32_t)m), "n"(LANE));
+  asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((uint32_t)(m >> 32)), "n"(LANE));
+}
 
 template <bool ROWS_TOO>
 __global__ __launch_bounds__(kListThreads) void k_block_lists(ListArgs a) {
@@ -549,17 +560,39 @@ __global__ __launch_bounds__(kListThreads) void k_block_lists(ListArgs a) {
       if (rc.y <= ty0 && ty0 <= rc.w) before += min(max(tx0 - rc.x, 0), w);
     }
     if (__ballot(n > 0 && rc.y <= ty1 && rc.w >= ty0 && rc.x <= xb && rc.z >= xa) != 0) {
+      // lane b keeps block b's ballot (there are at most 64), and one store takes them all
       int tx = tx0, ty = ty0;
-      for (int b = 0; b < nb; ++b) {
-        const uint64_t m = __ballot(rc.x <= tx && tx <= rc.z && rc.y <= ty && ty <= rc.w);
-        if (lane == 0) s_mask[b * chunks + c] = m;
+      uint32_t lo = 0, hi = 0;
+      uint64_t row = __ballot(rc.y <= ty && ty <= rc.w);
+      auto next = [&]() {
+        const uint64_t m = row & __ballot(rc.x <= tx && tx <= rc.z);
         if (++tx == sg.ntx) {
           tx = 0;
           ++ty;
+          row = __ballot(rc.y <= ty && ty <= rc.w);
         }
+        return m;
+      };
+      if (ROWS_TOO) {
+        for (int b = 0; b < nb; ++b) {
+          const uint64_t m = next();
+          lo = lane == b ? (uint32_t)m : lo;
+          hi = lane == b ? (uint32_t)(m >> 32) : hi;
+        }
+      } else {  // (blocks past nb are worked out and not stored)
+        write_lane<0>(next(), lo, hi);
+        write_lane<1>(next(), lo, hi);
+        write_lane<2>(next(), lo, hi);
+        write_lane<3>(next(), lo, hi);
+        write_lane<4>(next(), lo, hi);
+        write_lane<5>(next(), lo, hi);
+        write_lane<6>(next(), lo, hi);
+        write_lane<7>(next(), lo, hi);
+        static_assert(kListBlocks == 8, "a lane each");
       }
-    } else {
-      for (int b = lane; b < nb; b += 64) s_mask[b * chunks + c] = 0;
+      if (lane < nb) s_mask[lane * chunks + c] = (uint64_t)hi << 32 | lo;
+    } else if (lane < nb) {
+      s_mask[lane * chunks + c] = 0;
     }
   };
   const int4 none = make_int4(0, 0, -1, -1);
@@ -673,7 +706,26 @@ __global__ __launch_bounds__(kListThreads) void k_block_lists(ListArgs a) {
     int pos = __builtin_amdgcn_readfirstlane(s_list[b]);
     for (int c0 = 0; c0 < chunks; c0 += 64) {
       const uint64_t mine = c0 + lane < chunks ? s_mask[b * chunks + c0 + lane] : 0;
-      for (uint64_t left = __ballot(mine != 0); left != 0; left &= left - 1) {
+      uint64_t left = __ballot(mine != 0);
+      // Many chunks with an entry or two each (kernels in no order): a lane writes its own chunk's.
+      const int own = __popcll(mine);
+      if (__ballot(own > 4) == 0 && __popcll(left) > 4) {
+        int at = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const int o = __shfl_up(at, off);
+          if (lane >= off) at += o;
+        }
+        const int all = __builtin_amdgcn_readlane(at, 63);
+        at += pos - own;
+        for (uint64_t m = mine; m != 0; m &= m - 1, ++at) {
+          a.vals[at] = (uint32_t)(64 * (c0 + lane) + __builtin_ctzll(m));
+          a.keys[at] = (uint32_t)(t0 + b);
+        }
+        pos += all;
+        continue;
+      }
+      for (; left != 0; left &= left - 1) {
         const int c = __builtin_ctzll(left);
         const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)mine, c);
         const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(mine >> 32), c);
@@ -719,18 +771,20 @@ void preprocess(int C, int order, const float* params, const Segs& S, const smoe
 }
 
 // Rasters whose lists k_block_lists makes.  Measured, the binning by counters and sorts against
-// this one: 64 kernels on 64^2 16.9 / 7.0 us, 1024 on 256^2 17.7 / 9.3, 4096 on 512^2 18.5 /
-// 11.7, 8192 on 724^2 (2^24 pairs) 20.9 / 15.8, 16384 on 1024^2 (2^26) 22.8 / 24.4; wide kernels
-// are never slower, 2048 on 256^2 with 241 000 entries 167 / 15, 4000 on 512^2 with 620 000 entries
-// 116 / 18.  Of 4, 8 and 16 blocks to a workgroup eight are the best at 512^2 (12.7 / 11.7 / 13.1
-// us); four are 0.4 us faster at 256^2 and 7.7 us slower at 1024^2.
+// this one, kernels in the image's order / in random order: 64 kernels on 64^2 15.5 / 7.1 us and 15.0
+// / 7.1, 1024 on 256^2 16.4 / 9.0 and 18.4 / 9.7, 4096 on 512^2 18.0 / 11.6 and 19.9 / 13.0, 8192 on
+// 724^2 (2^24 pairs) 19.2 / 15.9 and 20.8 / 21.8, 16384 on 1024x512 (2^25) 24.1 / 21.7 and 25.6 /
+// 26.7 -- there the gain is the wide kernels': 16384 with 376 000 entries 76 / 24 and 63 / 38, 2048 on
+// 256^2 with 146 000 100 / 13 and 95 / 13, 4000 on 512^2 with 390 000 87 / 16 and 89 / 19.  Of 4, 8 and
+// 16 blocks to a workgroup eight are the best at 512^2 (12.7 / 11.7 / 13.1 us before the ballots were
+// gathered in lanes); four are 0.4 us faster at 256^2 and 7.7 us slower at 1024^2.
 constexpr int kListKernels = kListMasks / kListBlocks * 64, kListTiles = 4096;
 constexpr long long kListPairs = 1ll << 25;
 inline bool lists_by_block(const Segs& S) {
   return !S.tab && S.K > 0 && S.K <= kListKernels && S.T <= kListTiles &&
          (long long)S.K * S.T <= kListPairs;
 }
-// ... and by a single workgroup, with their rows: 16 ballots (64^2) 7.0 us and one launch,
+// ... and by a single workgroup, with their rows (at most 64 blocks): 16 ballots (64^2) 7.0 us and one launch,
 // 64 about the time of the two launches, 256 14.5 us against 8.5.
 inline bool lists_at_once(const Segs& S) {
   return S.K <= kListThreads && S.T <= kListThreads && cdiv(S.K, 64) * S.T <= 64;

@@ -15,7 +15,7 @@ constexpr int kNonfinite = 7;   // status word: a kernel row with a NaN or infin
 constexpr int kNonfiniteOut = 3;  // status word: the binning's copy of kNonfinite
 
 // Native 16x16 block index of a native coordinate, floor(x / 16) (x * 2^-4 is exact).
-__device__ __forceinline__ float native_block(float x) { return floorf(x * 0.0625f); }
+__host__ __device__ __forceinline__ float native_block(float x) { return floorf(x * 0.0625f); }
 
 // Output-block range [t0, t1] of one axis of a raster (n points sampled at
 // ((o + u) + 0.5) * inv_s; blocks aligned to multiples of 16 in o + u) holding a point whose
@@ -25,8 +25,9 @@ __device__ __forceinline__ float native_block(float x) { return floorf(x * 0.062
 // over the whole accepted range -- so both ends are had directly.  (A binary search over the
 // sample coordinates gives the same: 48 dependent steps per kernel at scale 4, 4096^2.)
 // False when no point is in [b0, b1] (or NaN).
-__device__ __forceinline__ bool output_axis(float b0, float b1, int n, int o, int scale,
-                                            float inv_s, int& t0, int& t1, int& nb0, int& nb1) {
+__host__ __device__ __forceinline__ bool output_axis(float b0, float b1, int n, int o, int scale,
+                                                     float inv_s, int& t0, int& t1, int& nb0,
+                                                     int& nb1) {
   const float first = native_block(sample_coord(0, o, inv_s));
   const float last = native_block(sample_coord(n - 1, o, inv_s));
   if (!(b1 >= first) || !(b0 <= last)) return false;

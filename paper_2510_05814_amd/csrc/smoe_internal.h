@@ -165,7 +165,7 @@ __device__ __forceinline__ SegGrid seg_of_kernel(const Segs& S, int j) {
 
 // Output pixel index -> native sampling coordinate, the exact binary32 sequence of the
 // ABI contract: ((o + u) + 0.5) * inv_s.
-__device__ __forceinline__ float sample_coord(int u, int o, float inv_s) {
+__host__ __device__ __forceinline__ float sample_coord(int u, int o, float inv_s) {
   return ((float)(o + u) + 0.5f) * inv_s;
 }
 

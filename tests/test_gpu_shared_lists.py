@@ -1,5 +1,5 @@
-"""Binning of batches by native block (scales of 2 to 8, whose scale^2 output blocks of a native
-block share their list) and, with a scale of 9 among them, by output block: rasters that begin and
+"""Binning of batches by native block (scales of 2 to 8, and with a scale of 9 among them, whose
+scale^2 output blocks of a native block share their list): rasters that begin and
 end inside a native block on either side of zero, scale-1 rasters beside them, lists of up to 64
 entries and of hundreds, rasters without kernels, and an overflow.  Every raster's arrays against
 the oracle's."""

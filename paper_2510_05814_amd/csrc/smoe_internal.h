@@ -60,8 +60,12 @@ struct Segs {
   int max_scale;                         // the largest scale of a segment
 };
 
-// A batch of rasters of a few blocks each (the windows of the multi-model estimator): a kernel
-// covers no more blocks than its raster has, and a block lists no more kernels.
+// A batch of rasters of a few blocks each on average (the windows of the multi-model estimator):
+// a kernel of a small raster covers few blocks and a block mostly lists few kernels, so there is
+// little for several lanes or waves to share out.  The average speaks for the whole batch: a
+// raster of 1024 blocks among a hundred of one block, or one-block rasters of 300 kernels each, go
+// the same way, which was the only way once (binning / render of the first 22.8 / 14.8 us before
+// there was another and 23.0 / 14.1 since, of the second 231 / 23.3 and 202 / 21.1).
 inline bool few_blocks(const Segs& S) { return S.tab && S.T / S.n < 16; }
 
 // Blocks of a raster: the 16x16 blocks of the output grid of its scale, aligned to

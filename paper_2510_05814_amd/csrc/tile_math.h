@@ -48,13 +48,15 @@ constexpr int kStrips = kTilePixels / kWave;   // 16x4 strips of a block (4)
 
 // Waves per block: one, or four (a strip each) on rasters whose blocks alone leave SIMDs idle
 // (1024 of them).  Four waves pay the column's terms four times over, one per SIMD waits on
-// its own latencies.  Measured, one wave against four, at 1024 / 1600 / 2025 / 2500 blocks:
-// RGB linear fit step 27.7 / 30.8 / 31.5 / 36.1 us against 24.7 / 32.1 / 34.6 / 39.3 (at 16 blocks
-// 23.8 against 18.2), render 14.3 / 13.9 / 13.9 / 14.6 against 13.9 / 15.1 / 17.4 / 19.4.  The
+// its own latencies.  Measured, one wave against four, at 1024 / 1369 / 1521 / 1600 / 1764 / 2025
+// blocks: RGB linear render 12.8 / 12.9 / 13.2 / 13.5 / 14.2 / 14.8 us against 10.5 / 12.8 / 13.1 /
+// 13.6 / 14.9 / 16.1, fit step 31.9 / 31.7 / 33.0 / 31.8 / 34.2 / 34.4 against 27.3 / 28.5 / 29.2 /
+// 32.0 / 33.0 / 35.1; grey constant render 10.8 / - / 11.0 / - / 11.6 / 11.9 against 7.6 / - / 8.8 / -
+// / 9.4 / 10.3, fit step 28.1 / - / 28.6 / - / 29.8 / 30.1 against 22.4 / - / 23.9 / - / 25.8 / 29.2.  The
 // backward alone has no such terms (its groups of entries are dealt out whole): 15.9 us against
 // 12.8 at 1024 blocks, 23.6 against 23.4 at 3600, 30.2 against 28.8 at 5184, 37.1 against 37.9 at
 // 7744.
-// Lists of a few entries (few_blocks) give four waves nothing to share: one (a fit of 1392
+// Batches of small rasters (few_blocks) mostly give four waves nothing to share: one (a fit of 1392
 // windows of a block each 22.6 us against 23.5).
 constexpr int kSplitForward = 1536, kSplitBackward = 6144;
 inline bool split_blocks(const Segs& S) { return S.T <= kSplitForward && !few_blocks(S); }

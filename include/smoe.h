@@ -437,7 +437,8 @@ smoe_status smoe_fuse_windows(const float* window_images, int32_t C, int32_t wid
 /* Synchronises `stream`, copies the status words (P needed, overflow flag, longest list,
  * non-finite flag) into host out4 (may be NULL) and returns SMOE_ERR_CAPACITY after an
  * overflow, else SMOE_ERR_NONFINITE when the last binning -- or, in a fit workspace, any step
- * of the fit so far -- met a kernel row with a NaN or infinite parameter. */
+ * of the fit so far -- met a kernel row with a NaN or infinite parameter.  SMOE_ERR_HIP on a
+ * stream under capture, which is left as it is. */
 smoe_status smoe_read_status(const smoe_bins* bins, int32_t* out4, void* stream);
 
 /* Name and description of the HIP error behind this thread's last SMOE_ERR_HIP ("no

@@ -1,6 +1,6 @@
 // Device building blocks shared by the standalone binning calls and the fused fit step:
-// the kernel box (Sec. IV-B), the render record, the per-block ordering of a bucket and the
-// block scan that turns per-block counts into list ranges (Sec. IV-C).  Internal header.
+// the kernel box (Sec. IV-B), the render record and the ordering of a block's list by kernel id
+// (Sec. IV-C).  Internal header.
 #pragma once
 
 #include "smoe_internal.h"
@@ -274,10 +274,12 @@ __device__ __forceinline__ void sort_runs(uint32_t* seg, uint32_t* alt, int n,
 // the ids' span / 32, against n log^2 n for a sorting network by one wave, which took 97 us over
 // 1024 lists of 500 to 900 ids; this takes 18 us.  Ids spread over more than kRunWindows windows, in
 // a list that fits a run, go by sort_runs (a million kernels in random order at 2048^2, lists of up
-// to 360: binning 810 -> 437 us, fit step 1580 -> 1096); longer lists do where the windows would
-// outlast the merges.
+// to 360: binning 810 -> 437 us, fit step 1580 -> 1096; at four windows bitmaps take 117 us where
+// runs take 131, at twelve 197 against 160).  Lists longer than a run do from kMergeWindows on:
+// bitmaps against merged runs, lists of about 2400 over 18 windows 973 / 984 us, of 6900 over 40
+// 3243 / 2832, of 5700 over 122 5532 / 2820.
 // All threads of the workgroup call it, with the same arguments; the result is in seg.
-constexpr uint32_t kRunWindows = 4, kMergeWindows = 64;
+constexpr uint32_t kRunWindows = 4, kMergeWindows = 24;
 template <int WAVES, int WINDOW, int RUN>
 __device__ __forceinline__ void sort_long(uint32_t* __restrict__ seg, uint32_t* __restrict__ alt, int n,
                                           int shift, LongSortScratch<WAVES, WINDOW, RUN>& sc) {

@@ -1,7 +1,7 @@
 """The ordering of block lists of more than 64 entries where its method changes: by counting up to
 192 (65, 191, 192 and 193 entries), by a bitmap over one and more windows of ids, by runs in LDS
 beyond four windows (lists of 257 to 2048), and by merged runs (more than
-64 windows and more entries than a run: 32768 ids a window and 2048 entries in the binning, 8192
+24 windows and more entries than a run: 32768 ids a window and 2048 entries in the binning, 8192
 and 512 in this fit).  Lists against the oracle; the fit's gradients against the standalone
 calls'."""
 import numpy as np
@@ -31,8 +31,8 @@ def spread(n, K, W, H, seed):
 @pytest.mark.parametrize("scale", [1, 2])
 @pytest.mark.parametrize("n,K", [(65, 65), (191, 300), (192, 70000), (193, 300), (193, 60000),
                                  (300, 120000), (193, 170000), (513, 170000), (1025, 170000),
-                                 (2047, 170000), (2048, 170000), (2049, 170000), (2500, 2200000),
-                                 (4100, 2200000)])
+                                 (2047, 170000), (2048, 170000), (2049, 170000), (2500, 700000),
+                                 (2500, 900000), (2500, 2200000), (4100, 2200000)])
 def test_lists_in_order(n, K, scale):
     import paper_2510_05814_amd as smoe
     say("sort runs", n, K, scale)
